@@ -6,9 +6,10 @@
 // both the depth of one v_mfma_f32_16x16x128_f8f6f4 and the length of one
 // scale block, so a blockwise step is one MFMA per 16 x 16 tile into a
 // zeroed partial, then one FMA per accumulator that adds S_A * S_B * P.
-// Four shapes are built: 256 x 256 tiles with eight waves of 128 x 64 (the
+// Five shapes are built: 256 x 256 tiles with eight waves of 128 x 64 (the
 // large-problem kernel: 64 FP8 bytes of LDS traffic per MFMA instead of
-// 128), 128 x 128 tiles with four waves of 64 x 64 (small grids, and the
+// 128), 128 x 256 tiles with eight waves of 64 x 64 (parts of its last
+// round, see large_tiles), 128 x 128 tiles with four waves of 64 x 64 (small grids, and the
 // (1x128, 1x128) pair whose per-column B scales need more registers), and
 // for skinny problems such as a decode step, 128 x 128 tiles with eight
 // waves of 32 x 64 and 64 x 64 tiles with four waves of 32 x 32, where a
@@ -425,6 +426,30 @@ __device__ __forceinline__ bool splitk_reduce(const GemmArgs& g, v4f (&acc)[TI][
   return true;
 }
 
+// LDS of a tile kernel: per K group a ring of kStages operand stages with
+// their scale vectors, and 256 bytes per wave (see gemm_tile).
+template <int PAIR, int BM, int BN, int WM, int WN, int KS = 1>
+struct TileLds {
+  static constexpr bool kBlockScaled = PAIR == kPairBlock || PAIR == kPairBlockK || PAIR == kPairBlockE8;
+  static constexpr bool kWeightBlocks = PAIR == kPairBlock || PAIR == kPairBlockE8;  // B scales per 128 x 128
+  static constexpr int kWaves = (BM / WM) * (BN / WN);
+  static constexpr int kStage = (BM + BN) * kBK;
+  // per-step scale vectors of the blockwise pairs, staged like the tiles:
+  // A row scales (BM floats) and B scales (the BN/128 weight-block scales,
+  // or BN column scales for 1x128 x 1x128)
+  static constexpr int kScaleA = kBlockScaled ? BM * 4 : 0;
+  static constexpr int kScaleB = PAIR == kPairBlockK ? BN * 4 : (kWeightBlocks ? 256 : 0);
+  // The loads of stage kt + kStages - 1 go out during step kt.  The 256 x
+  // 256 tile fits two 64 KB stages; 128 x 256 and 128 x 128 with waves of 64
+  // x 64 keep two (more would cost the latter its second workgroup per CU);
+  // the tiles of skinny problems, whose steps are short next to the load
+  // latency, keep four: 64 x 64, and 128 x 128 with eight waves of 32 x 64
+  // (one workgroup per CU).
+  static constexpr int kStages = (BM >= 128 && WM >= 64) ? 2 : 4;
+  static constexpr int kGroupBytes = kStages * (kStage + kScaleA + kScaleB);
+  static constexpr int kBytes = KS * (kGroupBytes + kWaves * 256);
+};
+
 // One workgroup computes a BM x BN tile of C with (BM/WM) x (BN/WN) waves,
 // each owning WM x WN as (WM/16) x (WN/16) MFMA tiles of 16 x 16.  QOUT: the
 // tile leaves as E4M3 codes and 1x128 scales of its bf16 values (see
@@ -439,35 +464,23 @@ __device__ __forceinline__ bool splitk_reduce(const GemmArgs& g, v4f (&acc)[TI][
 // (KT = K / 128 / g.splits); see splitk_reduce for how the partial tiles
 // meet.
 template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1, bool SPLITK = false>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int tm, int tn, int split = 0, int tile = 0) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, int tm, int tn, int split = 0,
+                                          int tile = 0) {
+  using Lds = TileLds<PAIR, BM, BN, WM, WN, KS>;  // lds_all: kBytes of it, 1024-byte aligned
   constexpr int kWavesN = BN / WN;
-  constexpr int kWaves = (BM / WM) * kWavesN;  // waves of one group
+  constexpr int kWaves = Lds::kWaves;  // waves of one group
   constexpr int TI = WM / 16, TJ = WN / 16;
-  constexpr int kTileA = BM * kBK, kTileB = BN * kBK, kStage = kTileA + kTileB;
+  constexpr int kTileA = BM * kBK, kStage = Lds::kStage;
   // kBlockScaled: per-K-step scale vectors are staged with the tiles;
   // kPromote: they are applied by FMAs on the VALU (fp32 scales), else the
   // accumulation runs in the MFMA accumulator (power-of-two scales enter
   // the instruction itself)
-  constexpr bool kBlockScaled = PAIR == kPairBlock || PAIR == kPairBlockK || PAIR == kPairBlockE8;
+  constexpr bool kBlockScaled = Lds::kBlockScaled;
   constexpr bool kPromote = PAIR == kPairBlock || PAIR == kPairBlockK;
-  constexpr bool kWeightBlocks = PAIR == kPairBlock || PAIR == kPairBlockE8;  // B scales per 128 x 128
-  // per-step scale vectors of the blockwise pairs, staged like the tiles:
-  // A row scales (BM floats) and B scales (the BN/128 weight-block scales,
-  // or BN column scales for 1x128 x 1x128)
-  constexpr int kScaleA = kBlockScaled ? BM * 4 : 0;
-  constexpr int kScaleB = PAIR == kPairBlockK ? BN * 4 : (kWeightBlocks ? 256 : 0);
-  constexpr int kScaleStage = kScaleA + kScaleB;
-  // LDS ring of kStages operand stages (and their scale vectors): the loads
-  // of stage kt + kStages - 1 go out during step kt.  The 256 x 256 tile
-  // fits two 64 KB stages; 128 x 128 with four waves of 64 x 64 keeps two
-  // (more would cost it its second workgroup per CU); the tiles of skinny
-  // problems, whose steps are short next to the load latency, keep four:
-  // 64 x 64, and 128 x 128 with eight waves of 32 x 64 (one workgroup per
-  // CU).
-  constexpr int kStages = (BM >= 128 && WM >= 64) ? 2 : 4;
+  constexpr bool kWeightBlocks = Lds::kWeightBlocks;
+  constexpr int kScaleA = Lds::kScaleA, kScaleB = Lds::kScaleB, kScaleStage = kScaleA + kScaleB;
+  constexpr int kStages = Lds::kStages, kGroupBytes = Lds::kGroupBytes;
   static_assert(KS == 1 || (kStages > 2 && !QOUT), "K groups: the 64 x 64 tile");
-  constexpr int kGroupBytes = kStages * kStage + kStages * kScaleStage;
-  __shared__ __attribute__((aligned(1024))) uint8_t lds_all[KS * kGroupBytes + KS * kWaves * 256];
   const int wave_all = uniform(threadIdx.x >> 6);
   const int kg = KS > 1 ? uniform(wave_all / kWaves) : 0;  // K group
   uint8_t* const lds = lds_all + kg * kGroupBytes;
@@ -1007,9 +1020,66 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int tm, int tn, int
 
 template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KS) void gemm_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[TileLds<PAIR, BM, BN, WM, WN, KS>::kBytes];
   int tm, tn;
   tile_coords<BM, BN>(g.M, g.N, g.K, blockIdx.x, tm, tn);
-  gemm_tile<PAIR, BM, BN, WM, WN, QOUT, FMT, KS>(g, tm, tn);
+  gemm_tile<PAIR, BM, BN, WM, WN, QOUT, FMT, KS>(g, lds, tm, tn);
+}
+
+// Large problems: 256 x 256 tiles, one per CU at a time, so the launch runs
+// in rounds of kCUs tiles and a last round with few tiles leaves most of the
+// chip idle for a whole tile's time.  The workgroups past `full` (a multiple
+// of kCUs, or every tile) therefore take a part of a tile each: the tiles at
+// raster positions full, full + 1, ... are cut into `parts` = 4 of 128 x 128
+// (eight waves of 32 x 64) or 2 of 128 x 256 (eight waves of 64 x 64), which
+// run on 4 or 2 times as many CUs for 0.4 or 0.62 of a tile's time (measured:
+// one round of each at K = 4096, 19, 33 and 56 us; blockwise 3001 x 5120 x
+// 17408, 3.2 rounds, 268 -> 242 us; power-of-two scales 4096 x 5120 x 17408,
+// 4.25 rounds, 321 -> 301 us; 2048 x 4096 x 12288, 1.5 rounds, 105 us on 128
+// x 128 tiles -> 95 us).  Every tile shape sums an output's K blocks in the
+// same order, so the cut changes no bit.
+constexpr int kCUs = 256;
+
+template <int PAIR>
+struct LargeLds {
+  static constexpr int kWhole = TileLds<PAIR, 256, 256, 128, 64>::kBytes, kHalf = TileLds<PAIR, 128, 256, 64, 64>::kBytes,
+                       kQuarter = TileLds<PAIR, 128, 128, 32, 64>::kBytes;
+  static constexpr int kMost = kWhole > kHalf ? kWhole : kHalf;
+  static constexpr int kBytes = kMost > kQuarter ? kMost : kQuarter;
+};
+
+// at(position, g, tm, tn): the problem and 256 x 256 tile of a raster position
+template <int PAIR, bool QOUT, int FMT, typename At>
+__device__ __forceinline__ void large_tiles(uint8_t* lds, int full, int parts, At&& at) {
+  const int b = blockIdx.x;
+  const GemmArgs* g;
+  int tm, tn;
+  if (b < full) {
+    at(xcd_order(full, b), g, tm, tn);
+    gemm_tile<PAIR, 256, 256, 128, 64, QOUT, FMT>(*g, lds, tm, tn);
+    return;
+  }
+  const int t = xcd_order((int)gridDim.x - full, b - full);  // (full % 8 == 0: the XCD is still b % 8)
+  const int part = t & (parts - 1);
+  at(full + (parts == 4 ? t >> 2 : t >> 1), g, tm, tn);
+  tm = 2 * tm + (part & 1);
+  if ((int64_t)tm * 128 >= g->M) return;  // (the whole workgroup: a part past the edge of C)
+  if (parts == 4) {
+    tn = 2 * tn + (part >> 1);
+    if ((int64_t)tn * 128 >= g->N) return;
+    gemm_tile<PAIR, 128, 128, 32, 64, QOUT, FMT>(*g, lds, tm, tn);
+  } else {
+    gemm_tile<PAIR, 128, 256, 64, 64, QOUT, FMT>(*g, lds, tm, tn);
+  }
+}
+
+template <int PAIR, bool QOUT, int FMT>
+__global__ __launch_bounds__(512) void gemm_large_kernel(GemmArgs args, int full, int parts) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[LargeLds<PAIR>::kBytes];
+  large_tiles<PAIR, QOUT, FMT>(lds, full, parts, [&](int id, const GemmArgs*& g, int& tm, int& tn) {
+    g = &args;
+    raster<256, 256>(args.M, args.N, args.K, id, tm, tn);
+  });
 }
 
 // Split-K: g.splits workgroups per 128 x 128 tile.  Positions run split by
@@ -1018,12 +1088,13 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KS) void gemm_kernel(G
 // a 256-row problem that share B rows on one XCD.
 template <int PAIR, int BM, int BN, int WM, int WN, int FMT>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_splitk_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[TileLds<PAIR, BM, BN, WM, WN>::kBytes];
   const int tiles = (int)((g.M + BM - 1) / BM) * (int)((g.N + BN - 1) / BN);
   const int id = xcd_order(tiles * g.splits, blockIdx.x);
   const int split = id / tiles, t = id - split * tiles;
   int tm, tn;
   raster<BM, BN>(g.M, g.N, g.K, t, tm, tn);
-  gemm_tile<PAIR, BM, BN, WM, WN, false, FMT, 1, true>(g, tm, tn, split, t);
+  gemm_tile<PAIR, BM, BN, WM, WN, false, FMT, 1, true>(g, lds, tm, tn, split, t);
 }
 
 // Grouped GEMM: one launch over several problems that share the pair, the
@@ -1031,14 +1102,28 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_splitk_kernel
 // operand, several weights and outputs).  The workgroups' XCD-ordered
 // positions run over the problems' rasters one after another; the problem
 // of a position is found from the prefix sums of the tile counts.
-template <int PAIR, int BM, int BN, int WM, int WN, int KS = 1>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KS) void gemm_grouped_kernel(GemmGroup gs) {
-  const int id = xcd_order(gs.tile_start[gs.count], blockIdx.x);
+template <int BM, int BN>
+__device__ __forceinline__ const GemmArgs* grouped_at(const GemmGroup& gs, int id, int& tm, int& tn) {
   int p = 0;
   for (int i = 1; i < gs.count; ++i) p += id >= gs.tile_start[i] ? 1 : 0;
-  int tm, tn;
   raster<BM, BN>(gs.prob[p].M, gs.prob[p].N, gs.prob[p].K, id - gs.tile_start[p], tm, tn);
-  gemm_tile<PAIR, BM, BN, WM, WN, false, 0, KS>(gs.prob[p], tm, tn);
+  return &gs.prob[p];
+}
+
+template <int PAIR, int BM, int BN, int WM, int WN, int KS = 1>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KS) void gemm_grouped_kernel(GemmGroup gs) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[TileLds<PAIR, BM, BN, WM, WN, KS>::kBytes];
+  int tm, tn;
+  const GemmArgs* g = grouped_at<BM, BN>(gs, xcd_order(gs.tile_start[gs.count], blockIdx.x), tm, tn);
+  gemm_tile<PAIR, BM, BN, WM, WN, false, 0, KS>(*g, lds, tm, tn);
+}
+
+template <int PAIR>
+__global__ __launch_bounds__(512) void gemm_grouped_large_kernel(GemmGroup gs, int full, int parts) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[LargeLds<PAIR>::kBytes];
+  large_tiles<PAIR, false, 0>(lds, full, parts, [&](int id, const GemmArgs*& g, int& tm, int& tn) {
+    g = grouped_at<256, 256>(gs, id, tm, tn);
+  });
 }
 
 template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1>
@@ -1047,6 +1132,45 @@ hipError_t launch_tiles(const GemmArgs& g, hipStream_t s) {
   if (tiles <= 0 || tiles > 0x7fffffff) return hipErrorInvalidValue;
   constexpr int threads = (BM / WM) * (BN / WN) * 64 * KS;
   gemm_kernel<PAIR, BM, BN, WM, WN, QOUT, FMT, KS><<<dim3((unsigned)tiles), threads, 0, s>>>(g);
+  return hipGetLastError();
+}
+
+// The grid of a large launch of `total` 256 x 256 tiles: `full` whole tiles,
+// then the rest in `parts` (see large_tiles).  The last round is cut when its
+// parts fit in one round of the CUs: up to a quarter of them in four, up to
+// half in two; a fuller last round keeps whole tiles.
+struct LargePlan {
+  int full, parts, grid, cost;
+};
+inline LargePlan large_plan(int64_t total) {
+  const int rest = (int)(total % kCUs), rounds = (int)(total / kCUs);
+  LargePlan p;
+  p.parts = rest == 0 || rest > kCUs / 2 ? 1 : (rest <= kCUs / 4 ? 4 : 2);
+  p.full = p.parts == 1 ? (int)total : rounds * kCUs;
+  p.grid = p.full + (p.parts == 1 ? 0 : rest * p.parts);
+  p.cost = 100 * rounds + (rest == 0 ? 0 : p.parts == 4 ? 40 : p.parts == 2 ? 62 : 90);
+  return p;
+}
+
+// Whether `big` 256 x 256 tiles run before `mid` 128 x 128 tiles (the same
+// outputs) would: both in percent of a whole 256 x 256 tile's time.  512 of
+// the 128 x 128 tiles (four waves, two workgroups per CU) take 59, up to 256
+// (one per CU) 37; a last round of whole 256 x 256 tiles on part of the chip
+// 90 (measured at K = 4096: 192 tiles 47 us, 256 tiles 56 us, 512 of 128 x
+// 128 33 us, 256 of them 20.6 us).
+inline bool takes_large(int64_t big, int64_t mid) {
+  if (big > 0x3fffffff / 100) return true;
+  const int64_t rest = mid % (2 * kCUs);
+  const int64_t cost_mid = 59 * (mid / (2 * kCUs)) + (rest == 0 ? 0 : rest <= kCUs ? 37 : 59);
+  return large_plan(big).cost < cost_mid;
+}
+
+template <int PAIR, bool QOUT, int FMT>
+hipError_t launch_large(const GemmArgs& g, hipStream_t s) {
+  const int64_t tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+  if (tiles <= 0 || tiles > 0x3fffffff) return hipErrorInvalidValue;
+  const LargePlan p = large_plan(tiles);
+  gemm_large_kernel<PAIR, QOUT, FMT><<<dim3((unsigned)p.grid), 512, 0, s>>>(g, p.full, p.parts);
   return hipGetLastError();
 }
 
@@ -1059,9 +1183,9 @@ inline bool k_groups(const GemmArgs& g) {
   return ((g.M + 63) / 64) * ((g.N + 63) / 64) <= 256 && (g.K / kBK) % 2 == 0;
 }
 
-// 256 x 256 tiles (8 waves of 128 x 64) when they fill the chip at least
-// twice over; else 128 x 128 tiles (4 waves of 64 x 64) when they fill it
-// once; else, for skinny problems such as a decode step, whose time goes
+// 256 x 256 tiles (8 waves of 128 x 64, see large_tiles) where they take less
+// time than 128 x 128 tiles (see takes_large); else 128 x 128 tiles (4 waves
+// of 64 x 64) when they fill the chip once; else, for skinny problems such as a decode step, whose time goes
 // into streaming the weights: 64 x 64 tiles with two K groups when those
 // fit (k_groups), 128 x 128 tiles of 8 waves of 32 x 64 with a four-stage
 // ring (one workgroup per CU) when there are 128 to 255 of them, and 64 x 64
@@ -1073,7 +1197,7 @@ hipError_t launch_pair(const GemmArgs& g, hipStream_t s) {
   const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
   const int64_t mid_tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
   if constexpr (PAIR != kPairBlockK) {
-    if (big_tiles >= 512) return launch_tiles<PAIR, 256, 256, 128, 64, QOUT, FMT>(g, s);
+    if (takes_large(big_tiles, mid_tiles)) return launch_large<PAIR, QOUT, FMT>(g, s);
   }
   if constexpr (QOUT) {
     return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
@@ -1148,11 +1272,8 @@ hipError_t launch_split(const GemmArgs& g, hipStream_t s) {
   template __global__ void gemm_kernel<PAIR, BM, BN, WM, WN, false, 1>(GemmArgs); \
   template __global__ void gemm_kernel<PAIR, BM, BN, WM, WN, false, 2>(GemmArgs); \
   template __global__ void gemm_kernel<PAIR, BM, BN, WM, WN, false, 3>(GemmArgs);
-FP8Q_GEMM_KERNEL(kPairTensor, 256, 256, 128, 64)
 FP8Q_GEMM_KERNEL(kPairTensor, 128, 128, 64, 64)
-FP8Q_GEMM_KERNEL(kPairRow, 256, 256, 128, 64)
 FP8Q_GEMM_KERNEL(kPairRow, 128, 128, 64, 64)
-FP8Q_GEMM_KERNEL(kPairBlock, 256, 256, 128, 64)
 FP8Q_GEMM_KERNEL(kPairBlock, 128, 128, 64, 64)
 FP8Q_GEMM_KERNEL(kPairBlockK, 128, 128, 64, 64)
 FP8Q_GEMM_KERNEL(kPairTensor, 128, 128, 32, 64)
@@ -1164,10 +1285,8 @@ FP8Q_GEMM_KERNEL(kPairTensor, 64, 64, 32, 32)
 FP8Q_GEMM_KERNEL(kPairRow, 64, 64, 32, 32)
 FP8Q_GEMM_KERNEL(kPairBlock, 64, 64, 32, 32)
 FP8Q_GEMM_KERNEL(kPairBlockK, 64, 64, 32, 32)
-FP8Q_GEMM_KERNEL(kPairBlockE8, 256, 256, 128, 64)
 FP8Q_GEMM_KERNEL(kPairBlockE8, 128, 128, 64, 64)
 FP8Q_GEMM_KERNEL(kPairBlockE8, 64, 64, 32, 32)
-FP8Q_GEMM_KERNEL_FMT(kPairBlock, 256, 256, 128, 64)
 FP8Q_GEMM_KERNEL_FMT(kPairBlock, 128, 128, 64, 64)
 FP8Q_GEMM_KERNEL_FMT(kPairBlock, 128, 128, 32, 64)
 FP8Q_GEMM_KERNEL_FMT(kPairBlockK, 128, 128, 32, 64)
@@ -1195,10 +1314,19 @@ FP8Q_GEMM_SPLITK(kPairRow)
 FP8Q_GEMM_SPLITK(kPairBlock)
 FP8Q_GEMM_SPLITK(kPairBlockK)
 #undef FP8Q_GEMM_SPLITK
-template __global__ void gemm_kernel<kPairBlock, 256, 256, 128, 64, true, 0>(GemmArgs);
+#define FP8Q_GEMM_LARGE(PAIR, QOUT, FMT) template __global__ void gemm_large_kernel<PAIR, QOUT, FMT>(GemmArgs, int, int);
+FP8Q_GEMM_LARGE(kPairTensor, false, 0)
+FP8Q_GEMM_LARGE(kPairRow, false, 0)
+FP8Q_GEMM_LARGE(kPairBlockE8, false, 0)
+FP8Q_GEMM_LARGE(kPairBlock, false, 0)
+FP8Q_GEMM_LARGE(kPairBlock, false, 1)
+FP8Q_GEMM_LARGE(kPairBlock, false, 2)
+FP8Q_GEMM_LARGE(kPairBlock, false, 3)
+FP8Q_GEMM_LARGE(kPairBlock, true, 0)
+#undef FP8Q_GEMM_LARGE
 template __global__ void gemm_kernel<kPairBlock, 128, 128, 64, 64, true, 0>(GemmArgs);
 #define FP8Q_GEMM_GROUPED(PAIR)                                                     \
-  template __global__ void gemm_grouped_kernel<PAIR, 256, 256, 128, 64>(GemmGroup);    \
+  template __global__ void gemm_grouped_large_kernel<PAIR>(GemmGroup, int, int);       \
   template __global__ void gemm_grouped_kernel<PAIR, 128, 128, 64, 64>(GemmGroup);     \
   template __global__ void gemm_grouped_kernel<PAIR, 64, 64, 32, 32>(GemmGroup);       \
   template __global__ void gemm_grouped_kernel<PAIR, 64, 64, 32, 32, 2>(GemmGroup);
@@ -1207,18 +1335,34 @@ FP8Q_GEMM_GROUPED(kPairRow)
 FP8Q_GEMM_GROUPED(kPairBlock)
 #undef FP8Q_GEMM_GROUPED
 
-template <int PAIR, int BM, int BN, int WM, int WN, int KS = 1>
-hipError_t launch_grouped_tiles(GemmGroup gs, hipStream_t s) {
+// tile_start of the group for BM x BN tiles; their number, -1 past 2^30 - 1
+template <int BM, int BN>
+int64_t count_tiles(GemmGroup& gs) {
   int64_t total = 0;
   for (int i = 0; i < gs.count; ++i) {
     gs.tile_start[i] = (int)total;
     total += ((gs.prob[i].M + BM - 1) / BM) * ((gs.prob[i].N + BN - 1) / BN);
-    if (total > 0x7fffffff) return hipErrorInvalidValue;
+    if (total > 0x3fffffff) return -1;
   }
   gs.tile_start[gs.count] = (int)total;
+  return total;
+}
+
+template <int PAIR, int BM, int BN, int WM, int WN, int KS = 1>
+hipError_t launch_grouped_tiles(GemmGroup gs, hipStream_t s) {
+  const int64_t total = count_tiles<BM, BN>(gs);
   if (total <= 0) return hipErrorInvalidValue;
   constexpr int threads = (BM / WM) * (BN / WN) * 64 * KS;
   gemm_grouped_kernel<PAIR, BM, BN, WM, WN, KS><<<dim3((unsigned)total), threads, 0, s>>>(gs);
+  return hipGetLastError();
+}
+
+template <int PAIR>
+hipError_t launch_grouped_large(GemmGroup gs, hipStream_t s) {
+  const int64_t total = count_tiles<256, 256>(gs);
+  if (total <= 0) return hipErrorInvalidValue;
+  const LargePlan p = large_plan(total);
+  gemm_grouped_large_kernel<PAIR><<<dim3((unsigned)p.grid), 512, 0, s>>>(gs, p.full, p.parts);
   return hipGetLastError();
 }
 
@@ -1237,7 +1381,7 @@ hipError_t launch_grouped_pair(const GemmGroup& gs, hipStream_t s) {
     const GemmArgs& g = gs.prob[i];
     const int64_t big_i = ((g.M + 255) / 256) * ((g.N + 255) / 256);
     const int64_t mid_i = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-    if (big_i < 512 && mid_i < 256 && k_groups(g)) {
+    if (!takes_large(big_i, mid_i) && mid_i < 256 && k_groups(g)) {
       thin.prob[thin.count++] = g;
     } else {
       tiled.prob[tiled.count++] = g;
@@ -1246,9 +1390,9 @@ hipError_t launch_grouped_pair(const GemmGroup& gs, hipStream_t s) {
     }
   }
   if (tiled.count) {
-    const hipError_t e = big >= 512   ? launch_grouped_tiles<PAIR, 256, 256, 128, 64>(tiled, s)
-                         : mid >= 256 ? launch_grouped_tiles<PAIR, 128, 128, 64, 64>(tiled, s)
-                                      : launch_grouped_tiles<PAIR, 64, 64, 32, 32>(tiled, s);
+    const hipError_t e = takes_large(big, mid) ? launch_grouped_large<PAIR>(tiled, s)
+                         : mid >= 256          ? launch_grouped_tiles<PAIR, 128, 128, 64, 64>(tiled, s)
+                                               : launch_grouped_tiles<PAIR, 64, 64, 32, 32>(tiled, s);
     if (e != hipSuccess) return e;
   }
   if (thin.count) return launch_grouped_tiles<PAIR, 64, 64, 32, 32, 2>(thin, s);
