@@ -9,9 +9,8 @@
 // Five shapes are built: 256 x 256 tiles with eight waves of 128 x 64 (the
 // large-problem kernel: 64 FP8 bytes of LDS traffic per MFMA instead of
 // 128), 128 x 256 tiles with eight waves of 64 x 64 (parts of its last
-// round, see large_tiles), 128 x 128 tiles with four waves of 64 x 64 (small grids, and the
-// (1x128, 1x128) pair whose per-column B scales need more registers), and
-// for skinny problems such as a decode step, 128 x 128 tiles with eight
+// round, see large_tiles), 128 x 128 tiles with four waves of 64 x 64 (small
+// grids), and for skinny problems such as a decode step, 128 x 128 tiles with eight
 // waves of 32 x 64 and 64 x 64 tiles with four waves of 32 x 32, where a
 // few tiles split their K blocks over two groups of waves.
 //
@@ -215,6 +214,9 @@ __device__ __forceinline__ void lds_read_f32x4(uint32_t addr, float (&v)[4]) {
   asm volatile("ds_read_b128 %0, %1" : "=v"(t) : "v"(addr));
   v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
 }
+
+// After an LDS wait that covers v's read: v counts as written here.
+__device__ __forceinline__ void lds_arrived(float& v) { asm volatile("" : "+v"(v)); }
 
 // Wait until at most N LDS reads of this wave are outstanding, and make
 // `f` (whose reads were issued before the last N) count as written here.
@@ -622,7 +624,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, i
   constexpr int kPerStripB = (kPerB + TI / 2 - 1) / (TI / 2);        // strips TI/2 .. TI-1
   static_assert(kQ <= kWaves, "at most one scale-vector load per wave and step");
   // LDS reads of the step's scales, issued after the first strip's MFMAs
-  constexpr int kScaleReads = PAIR == kPairBlock ? TI + 1 : (PAIR == kPairBlockK ? TI + TJ : 0);
+  constexpr int kScaleReads = PAIR == kPairBlock ? TI + 1 : (PAIR == kPairBlockK ? TJ + 2 : 0);
   static_assert(kScaleReads + 2 <= 15, "outstanding LDS reads must fit the lgkm counter");
 
   // One K step; kMore: the loads of stage kt + kStages - 1 go out during
@@ -749,31 +751,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, i
     };
 
     float sa[TI], sb[TJ][4], sb0 = 0.f;
-    auto read_scales = [&]() {
-      if (kBlockScaled) {
-        const uint32_t a_addr = lds_addr(cur_scales) + (wm + (lane & 15)) * 4;
+    auto read_scales = [&]() {  // kPairBlock
 #pragma unroll
-        for (int i = 0; i < TI; ++i) sa[i] = lds_read_f32(a_addr, i * 64);
-      }
-      if (PAIR == kPairBlock) sb0 = lds_read_f32(lds_addr(cur_scales + kScaleA) + (wn / 128) * 4, 0);
-      if (PAIR == kPairBlockK) {
-        const uint32_t b_addr = lds_addr(cur_scales + kScaleA) + (wn + (lane >> 4) * 4) * 4;
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) lds_read_f32x4(b_addr + j * 64, sb[j]);
-      }
+      for (int i = 0; i < TI; ++i) sa[i] = lds_read_f32(sa_addr, i * 64);
+      sb0 = lds_read_f32(lds_addr(cur_scales + kScaleA) + (wn / 128) * 4, 0);
     };
     auto scales_ready = [&]() {  // after an lgkm wait that covers the scale reads
-      if (kBlockScaled) {
 #pragma unroll
-        for (int i = 0; i < TI; ++i) asm volatile("" : "+v"(sa[i]));
-      }
-      if (PAIR == kPairBlock) asm volatile("" : "+v"(sb0));
-      if (PAIR == kPairBlockK) {
-#pragma unroll
-        for (int j = 0; j < TJ; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) asm volatile("" : "+v"(sb[j][r]));
-      }
+      for (int i = 0; i < TI; ++i) asm volatile("" : "+v"(sa[i]));
+      asm volatile("" : "+v"(sb0));
     };
 
     if constexpr (!kPromote) {
@@ -820,6 +806,68 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, i
         af_next = af_after;
       });
       done = acc[TI - 1][TJ - 1][3] * 0.0f;
+    } else if constexpr (PAIR == kPairBlockK) {
+      // Two vector operations per output and K block (the row scale, then
+      // the column scale in the FMA): as many cycles as the matrix
+      // instructions, so they go out in turn, the partial of strip i + 1,
+      // tile j, then the eight operations of strip i, tile j.  The fragments
+      // rotate as below; a partial's registers are free for the next but one
+      // matrix instruction, so TJ + 1 partials are live, and the row scales
+      // are read from LDS a strip ahead instead of all at once: that leaves
+      // the 256 x 256 tile its 128 accumulators and 16 column scales (250
+      // registers; with four matrix instructions before their 32 operations,
+      // as below, it spilled).  The matrix pipe takes about four of these
+      // operations under one instruction for free and each further one costs
+      // it four cycles (register-only probe: 32 cycles with none or four, 45
+      // with eight), which binds this pair.  4096 x 8192 x 12288 on 128 x 128
+      // tiles 455 us, here 400; 25600 x 16384 x 5120 2384 and 2180.
+      const v4f zero = {0.f, 0.f, 0.f, 0.f};
+      v4f p[TJ];
+      static_for<TJ>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        wait_b(jc);
+        p[j] = mfma_16x16x128<FMT>(bf[j], af, zero);
+        sched_fence();
+      });
+      mid_barrier();
+      const uint32_t b_addr = lds_addr(cur_scales + kScaleA) + (wn + (lane >> 4) * 4) * 4;
+      static_for<TJ>([&](auto j) { lds_read_f32x4(b_addr + decltype(j)::value * 64, sb[decltype(j)::value]); });
+      float sa_i = lds_read_f32(sa_addr, 0), sa_n = 0.f;
+      static_for<TI>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        constexpr int kAfter = (i + 1 < TI ? 1 : 0) + (i + 2 < TI ? 2 : 0);  // reads of sa_n and af_after
+        if constexpr (i + 1 < TI) sa_n = lds_read_f32(sa_addr, (i + 1) * 64);
+        v8i af_after = af_next;
+        if constexpr (i + 2 < TI)
+          af_after = read_frag<(i + 2) * 2048>(fa, af, af_next, i > 0 ? acc[i > 0 ? i - 1 : 0][TJ - 1][3] : done);
+        if constexpr (i + 1 < TI) {
+          if constexpr (i > 0) order_after(af_next, acc[i - 1]);
+          lds_wait<kAfter>(af_next);  // with it sa_i, and in strip 0 the column scales
+        } else {
+          asm volatile("s_waitcnt lgkmcnt(0)");
+          sched_fence();
+          issue_strip(ic);
+        }
+        lds_arrived(sa_i);
+        if constexpr (i == 0)
+          static_for<TJ * 4>([&](auto qc) { lds_arrived(sb[decltype(qc)::value / 4][decltype(qc)::value % 4]); });
+        static_for<TJ>([&](auto jc) {
+          constexpr int j = decltype(jc)::value;
+          v4f p_next = p[j];
+          if constexpr (i + 1 < TI) {
+            p_next = mfma_16x16x128<FMT>(bf[j], af_next, zero);
+            after_mfma(ic, jc);
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[i][j][r] = __builtin_fmaf(p[j][r] * sa_i, sb[j][r], acc[i][j][r]);
+          sched_fence();
+          p[j] = p_next;
+        });
+        sa_i = sa_n;
+        af = af_next;
+        af_next = af_after;
+      });
+      done = acc[TI - 1][TJ - 1][3];
     } else {
       // Row strips of the wave tile, software pipelined: the MFMAs of strip
       // i+1 (into zeroed partials) are issued before the FMAs that fold the
@@ -866,17 +914,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, i
           asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(kAfter));
           scales_ready();
         }
-        const float si = PAIR == kPairBlock ? sa[i] * sb0 : sa[i];
+        const float si = sa[i] * sb0;
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) {
+        for (int j = 0; j < TJ; ++j)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            if (PAIR == kPairBlock)
-              acc[i][j][r] = __builtin_fmaf(p[j][r], si, acc[i][j][r]);
-            else
-              acc[i][j][r] = __builtin_fmaf(p[j][r] * si, sb[j][r], acc[i][j][r]);
-          }
-        }
+          for (int r = 0; r < 4; ++r) acc[i][j][r] = __builtin_fmaf(p[j][r], si, acc[i][j][r]);
 #pragma unroll
         for (int j = 0; j < TJ; ++j) p[j] = p_next[j];
         af = af_next;
@@ -1196,9 +1238,7 @@ template <int PAIR, bool QOUT, int FMT>
 hipError_t launch_pair(const GemmArgs& g, hipStream_t s) {
   const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
   const int64_t mid_tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-  if constexpr (PAIR != kPairBlockK) {
-    if (takes_large(big_tiles, mid_tiles)) return launch_large<PAIR, QOUT, FMT>(g, s);
-  }
+  if (takes_large(big_tiles, mid_tiles)) return launch_large<PAIR, QOUT, FMT>(g, s);
   if constexpr (QOUT) {
     return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
   } else {
@@ -1323,6 +1363,10 @@ FP8Q_GEMM_LARGE(kPairBlock, false, 1)
 FP8Q_GEMM_LARGE(kPairBlock, false, 2)
 FP8Q_GEMM_LARGE(kPairBlock, false, 3)
 FP8Q_GEMM_LARGE(kPairBlock, true, 0)
+FP8Q_GEMM_LARGE(kPairBlockK, false, 0)
+FP8Q_GEMM_LARGE(kPairBlockK, false, 1)
+FP8Q_GEMM_LARGE(kPairBlockK, false, 2)
+FP8Q_GEMM_LARGE(kPairBlockK, false, 3)
 #undef FP8Q_GEMM_LARGE
 template __global__ void gemm_kernel<kPairBlock, 128, 128, 64, 64, true, 0>(GemmArgs);
 #define FP8Q_GEMM_GROUPED(PAIR)                                                     \

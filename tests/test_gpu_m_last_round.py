@@ -21,7 +21,7 @@ DEV = "cuda:0"
 K = 384                                # odd number of K blocks: no K groups in the strips
 # (tile rows, tile columns): 257, 320 (quarters), 321, 384 (halves), 385 (whole)
 GRIDS = [(257, 1), (20, 16), (107, 3), (24, 16), (77, 5)]
-FORMS = ["tensor", "row", "block", "pow2", "e5m2", "quantized", "grouped"]
+FORMS = ["tensor", "row", "block", "blockk", "pow2", "e5m2", "quantized", "grouped"]
 
 
 def call(form, a, sa, b, sb, strip=False):
@@ -46,7 +46,7 @@ def call(form, a, sa, b, sb, strip=False):
 @pytest.mark.parametrize("form", FORMS)
 def test_last_round_equals_strips(form, grid):
     tm, tn = grid
-    M, N = 256 * tm - 71, 256 * tn - (60 if form in ("tensor", "row") else 128)
+    M, N = 256 * tm - 71, 256 * tn - (60 if form in ("tensor", "row", "blockk") else 128)
     ga, gb = PAIRS[form] if form in PAIRS else PAIRS["block"]
     x = synth.activations(M, K, seed=501, outlier_seed=502, device=DEV)
     w = synth.weights(N, K, seed=503, device=DEV)
@@ -64,10 +64,12 @@ def test_last_round_equals_strips(form, grid):
             assert torch.equal(got[1].view(N // 128, M)[:, r:e], want[1].view(N // 128, e - r))
 
 
+@pytest.mark.parametrize("pair", ["block", "blockk"])
 @pytest.mark.parametrize("grid", GRIDS[1:4])
-def test_last_round_against_oracle(grid):
-    M, N = 256 * grid[0] - 71, 256 * grid[1] - 128
+def test_last_round_against_oracle(pair, grid):
+    """(blockk: its 256 x 256 tiles too, with their column scales)"""
+    M, N = 256 * grid[0] - 71, 256 * grid[1] - (128 if pair == "block" else 60)
     a = synth.activations(M, K, seed=511, outlier_seed=512, device=DEV)
     b = synth.weights(N, K, seed=513, device=DEV)
     rows = np.unique(np.concatenate([np.arange(0, M, 509), np.arange(M - 12, M)]))
-    run_pair(a, b, *PAIRS["block"], rows=rows, label="last round %dx%d" % grid)
+    run_pair(a, b, *PAIRS[pair], rows=rows, label="%s last round %dx%d" % (pair, *grid))
