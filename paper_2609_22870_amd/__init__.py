@@ -1,14 +1,20 @@
 """fp8q: FP8 scaled quantization (paper Sec. 2.2, Eq. 3) and the scaled FP8
 GEMM of the FP8 linear layer, as hand-written HIP kernels for MI355X (gfx950).
 
-This module is a thin ctypes binding over the C-ABI of ``libfp8q.so``
-(declared in ``include/fp8q.h``): it only marshals arguments.  PyTorch is
-used for device memory and the current HIP stream; every step of the
-computation runs in the library's kernels.  There is no fallback: if the
-library is missing, every call raises.
+This module is a thin binding over the C-ABI of ``libfp8q.so`` (declared in
+``include/fp8q.h``): it only marshals arguments.  PyTorch is used for device
+memory and the current HIP stream; every step of the computation runs in the
+library's kernels.  There is no fallback: if the library is missing, every
+call raises.
+
+Each wrapper first hands its arguments to the function of ``_native.so``
+(csrc/binding.cpp) that checks, allocates and calls the C-ABI in native code;
+that takes ordinary calls and returns None for any other, which the Python
+code below then makes, or refuses with the error that says why.
 """
 import ctypes
 import os
+import struct
 
 import torch
 
@@ -57,6 +63,10 @@ class ClipResult(ctypes.Structure):
                    ("l_updated", ctypes.c_int32), ("h_updated", ctypes.c_int32)])
 
 
+_CLIP_FIELDS = tuple(n for n, _ in ClipResult._fields_)
+_CLIP_STRUCT = struct.Struct("=7d2q2i")
+
+
 # Sec. 4 settings, with the GRPO experiments' reference bounds (Sec. 5.1).
 PAPER_CLIP_CONFIG = dict(c_low_ref=0.8, c_high_ref=1.24, l_min=0.5, l_max=0.9, h_min=1.2,
                          h_max=2.0, step=0.02, delta_l=0.05, delta_h=0.1)
@@ -69,15 +79,21 @@ class Fp8qError(RuntimeError):
 
 
 _lib = None
+_calls = None
+# the entry points of binding.cpp's Api, in its order
+_NATIVE_API = ("fp8q_scales_count", "fp8q_quantize", "fp8q_quantize_dual", "fp8q_gemm_formats", "fp8q_gemm_grouped",
+               "fp8q_gemm_pow2", "fp8q_gemm_quantized", "fp8q_gemm_splitk_workspace", "fp8q_gemm_splitk",
+               "fp8q_calibrate_clip_workspace", "fp8q_calibrate_clip")
 
 
 def lib():
     """Load libfp8q.so (built by __graft_entry__.build()); raise if absent."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError("libfp8q.so is not built (%s); run "
                               "__graft_entry__.build()" % LIB_PATH)
+        from . import _native as native  # ImportError when it is not built
         L = ctypes.CDLL(LIB_PATH)
         p, i64, i32, u32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_uint
         L.fp8q_scales_count.argtypes = [i64, i64, i32, u32]
@@ -117,6 +133,8 @@ def lib():
         L.fp8q_cast_f32.restype = i32
         L.fp8q_status_string.argtypes = [i32]
         L.fp8q_status_string.restype = ctypes.c_char_p
+        native.bind(tuple(ctypes.cast(getattr(L, n), p).value for n in _NATIVE_API))
+        _calls = native
         _lib = L
     return _lib
 
@@ -128,9 +146,23 @@ def status_string(status):
         return _STATUS.get(status, str(status))
 
 
+def _fast():
+    """The native entry points (the library loaded)."""
+    if _lib is None:
+        lib()
+    return _calls
+
+
 def _check(status, what):
     if status != 0:
         raise Fp8qError(status, what)
+
+
+def _done(r, what):
+    """The native call's outputs, or its status as an error."""
+    if type(r) is int:
+        raise Fp8qError(r, what)
+    return r
 
 
 def _stream(t):
@@ -198,6 +230,10 @@ def quantize(x, granularity, transposed=False, codes=None, scales=None, pow2=Fal
     include/fp8q.h.  pow2: power-of-two scales (FP8Q_POW2_SCALE); e5m2:
     E5M2 codes (FP8Q_E5M2).
     """
+    flags = (OUT_TRANSPOSED if transposed else 0) | (POW2_SCALE if pow2 else 0) | (E5M2 if e5m2 else 0)
+    r = _fast().quantize(x, granularity, flags, codes, scales)
+    if r is not None:
+        return _done(r, "fp8q_quantize")
     _matrix(x, torch.bfloat16, "x")
     rows, cols = x.shape
     oshape = (cols, rows) if transposed else (rows, cols)
@@ -208,9 +244,7 @@ def quantize(x, granularity, transposed=False, codes=None, scales=None, pow2=Fal
     if scales is None:
         scales = torch.empty(n, dtype=torch.float32, device=x.device)
     _vector(scales, torch.float32, n, "scales", x.device)
-    st = lib().fp8q_quantize(x.data_ptr(), rows, cols, _ld(x), granularity,
-                             (OUT_TRANSPOSED if transposed else 0) | (POW2_SCALE if pow2 else 0)
-                             | (E5M2 if e5m2 else 0),
+    st = lib().fp8q_quantize(x.data_ptr(), rows, cols, _ld(x), granularity, flags,
                              codes.data_ptr(), _ld(codes), scales.data_ptr(),
                              _stream(x))
     _check(st, "fp8q_quantize")
@@ -222,6 +256,10 @@ def quantize_dual(x, codes_r=None, scales_r=None, codes_t=None, scales_t=None, p
     one read: (codes_r, scales_r) = quantize(x, BLOCK_1x128) and
     (codes_t, scales_t) = quantize(x, BLOCK_128x1, transposed=True), with
     the same pow2 / e5m2 options."""
+    flags = (POW2_SCALE if pow2 else 0) | (E5M2 if e5m2 else 0)
+    r = _fast().quantize_dual(x, flags, codes_r, scales_r, codes_t, scales_t)
+    if r is not None:
+        return _done(r, "fp8q_quantize_dual")
     _matrix(x, torch.bfloat16, "x")
     rows, cols = x.shape
     nr, nt = scales_count(rows, cols, BLOCK_1x128), scales_count(rows, cols, BLOCK_128x1, True)
@@ -237,8 +275,7 @@ def quantize_dual(x, codes_r=None, scales_r=None, codes_t=None, scales_t=None, p
     _matrix(codes_t, torch.uint8, "codes_t", (cols, rows), x.device)
     _vector(scales_r, torch.float32, nr, "scales_r", x.device)
     _vector(scales_t, torch.float32, nt, "scales_t", x.device)
-    st = lib().fp8q_quantize_dual(x.data_ptr(), rows, cols, _ld(x),
-                                  (POW2_SCALE if pow2 else 0) | (E5M2 if e5m2 else 0),
+    st = lib().fp8q_quantize_dual(x.data_ptr(), rows, cols, _ld(x), flags,
                                   codes_r.data_ptr(), _ld(codes_r),
                                   scales_r.data_ptr(), codes_t.data_ptr(),
                                   _ld(codes_t), scales_t.data_ptr(), _stream(x))
@@ -252,6 +289,9 @@ def gemm(a, sa, ga, b, sb, gb, out=None):
     a, b: uint8 E4M3 codes, K contiguous; sa, sb: fp32 scales for the
     granularities ga, gb (pairs listed in include/fp8q.h).
     """
+    r = _fast().gemm(a, sa, ga, b, sb, gb, 0, out)
+    if r is not None:
+        return _done(r, "fp8q_gemm")
     M, N, K = _operands(a, sa, ga, b, sb, gb)
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
@@ -278,6 +318,9 @@ def gemm_splitk(a, sa, ga, b, sb, gb, out=None, workspace=None):
     of at least gemm_splitk_workspace(M, N, K) bytes, zero-filled before its
     first use (a new zero-filled one when None); calls sharing it must be
     ordered (one stream)."""
+    r = _fast().gemm_splitk(a, sa, ga, b, sb, gb, out, workspace)
+    if r is not None:
+        return _done(r, "fp8q_gemm_splitk")
     M, N, K = _operands(a, sa, ga, b, sb, gb)
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
@@ -300,6 +343,9 @@ def gemm_grouped(problems, ga, gb, outs=None):
     problems: list of (a, sa, b, sb) with one K and the granularities ga,
     gb for all (the a's may be the same tensor); returns the bf16 outputs
     (or fills `outs`)."""
+    r = _fast().gemm_grouped(problems, ga, gb, outs)
+    if r is not None:
+        return _done(r, "fp8q_gemm_grouped")
     if not 1 <= len(problems) <= MAX_GROUP:
         raise ValueError("1 .. %d problems" % MAX_GROUP)
     K = problems[0][0].shape[1]
@@ -326,6 +372,9 @@ def gemm_grouped(problems, ga, gb, outs=None):
 def gemm_formats(a, sa, ga, b, sb, gb, formats, out=None):
     """gemm() with E5M2 codes for A (formats & A_E5M2) and/or B (formats &
     B_E5M2): the backward pairs (1x128, 128x128) and (1x128, 1x128)."""
+    r = _fast().gemm(a, sa, ga, b, sb, gb, formats, out)
+    if r is not None:
+        return _done(r, "fp8q_gemm_formats")
     M, N, K = _operands(a, sa, ga, b, sb, gb)
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
@@ -340,6 +389,9 @@ def gemm_formats(a, sa, ga, b, sb, gb, formats, out=None):
 def gemm_pow2(a, sa, ga, b, sb, gb, out=None):
     """gemm() for operands quantized with power-of-two scales (pow2=True):
     the block scales enter the matrix instruction as exponents."""
+    r = _fast().gemm_pow2(a, sa, ga, b, sb, gb, out)
+    if r is not None:
+        return _done(r, "fp8q_gemm_pow2")
     M, N, K = _operands(a, sa, ga, b, sb, gb)
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
@@ -356,6 +408,9 @@ def gemm_quantized(a, sa, ga, b, sb, gb, codes=None, scales=None):
     (the next layer's activation operand), in one kernel.  Returns (codes
     uint8 [M, N], scales fp32 in the 1x128 layout), exactly
     quantize(gemm(a, sa, ga, b, sb, gb), BLOCK_1x128)."""
+    r = _fast().gemm_quantized(a, sa, ga, b, sb, gb, codes, scales)
+    if r is not None:
+        return _done(r, "fp8q_gemm_quantized")
     M, N, K = _operands(a, sa, ga, b, sb, gb)
     n = scales_count(M, N, BLOCK_1x128)
     if codes is None:
@@ -380,12 +435,21 @@ def calibrate_clip(adv, w_tis, pi_sampler, r_bf16, r_fp8, l_old, h_old, config=N
     dict (reading it back waits for the kernels); `result` may be a uint8
     CUDA tensor of ctypes.sizeof(ClipResult) bytes to write into, and with
     read=False nothing is read back (the call returns None)."""
+    cfg = ClipConfig(**(config or PAPER_CLIP_CONFIG))
+    r = _fast().calibrate_clip(adv, w_tis, pi_sampler, r_bf16, r_fp8, l_old, h_old, ctypes.addressof(cfg),
+                               workspace, result, bool(read))
+    if r is not None:
+        r = _done(r, "fp8q_calibrate_clip")
+        if r is True:
+            return None
+        if isinstance(r, torch.Tensor):
+            r = r.cpu().numpy().tobytes()
+        return dict(zip(_CLIP_FIELDS, _CLIP_STRUCT.unpack_from(r)))
     ts = (adv, w_tis, pi_sampler, r_bf16, r_fp8)
     n = adv.numel()
     for t in ts:
         if t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous() or t.numel() != n:
             raise ValueError("inputs must be contiguous float32 CUDA tensors of one length")
-    cfg = ClipConfig(**(config or PAPER_CLIP_CONFIG))
     need = lib().fp8q_calibrate_clip_workspace(n)
     if need < 0:
         raise ValueError("empty batch")

@@ -1,4 +1,5 @@
-"""Builds libfp8q.so (the HIP kernels and the C-ABI) for gfx950 with hipcc."""
+"""Builds libfp8q.so (the HIP kernels and the C-ABI) for gfx950 with hipcc,
+and _native.so (the binding's native code, host only) against PyTorch."""
 import os
 import subprocess
 from concurrent.futures import ThreadPoolExecutor
@@ -8,6 +9,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libfp8q.so")
+NATIVE = os.path.join(PKG, "_native.so")
 SOURCES = ["abi.hip", "quantize.hip", "gemm.hip", "clip.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -40,6 +42,33 @@ def check_no_scratch(src, remarks):
                 raise RuntimeError("%s: %s spills to scratch (%d bytes per lane)" % (src, name, size))
 
 
+def build_native():
+    """_native.so: csrc/binding.cpp against the installed PyTorch's headers and
+    libraries (already loaded by the package's `import torch` when it is)."""
+    import sysconfig
+
+    import torch
+
+    t = os.path.dirname(torch.__file__)
+    tmp = NATIVE + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi()),
+           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-I", INCLUDE, os.path.join(CSRC, "binding.cpp"), "-o", tmp,
+           "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("%s failed for binding.cpp:\n%s" % (cmd[0], r.stderr))
+    r = subprocess.run(["python3", "-c", "import ctypes, sys, torch; ctypes.CDLL(sys.argv[1])", tmp],
+                       capture_output=True, text=True)
+    if r.returncode != 0:
+        os.unlink(tmp)
+        raise RuntimeError("built binding does not load:\n%s" % r.stderr)
+    os.replace(tmp, NATIVE)
+
+
 def build():
     objdir = os.path.join(PKG, "_build")
     os.makedirs(objdir, exist_ok=True)
@@ -53,8 +82,10 @@ def build():
         check_no_scratch(src, r.stderr)
         return obj
 
-    with ThreadPoolExecutor(len(SOURCES)) as ex:
+    with ThreadPoolExecutor(len(SOURCES) + 1) as ex:
+        native = ex.submit(build_native)
         objs = list(ex.map(compile_one, SOURCES))
+        native.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
