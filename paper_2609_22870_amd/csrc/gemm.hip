@@ -1060,6 +1060,175 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, i
   }
 }
 
+// Thin problems (a decode step of a few sequences, small layers): too few
+// outputs to give every CU a tile worth sharing between waves, and the time is
+// the latency of the tile kernels' step chain (barrier, fragment reads, matrix
+// instructions, FMAs) times K.  Here every wave is on its own: the kThinWaves
+// waves of a workgroup take the K blocks w, w + 8, ... of one small tile, each
+// through an LDS stage of its own (loaded straight to LDS in whole 128-byte
+// rows, read into registers, and loaded again while its matrix instructions
+// run), with no barrier until their partial tiles meet in LDS, added in wave
+// order.  Every tile size sums an output's K blocks in this one order.
+// Measured (us a call, before: the 64 x 64 tile with two K groups): 8 x 4096
+// x 6144 9.3 -> 6.3, 16 x 12288 x 4096 20.8 -> 9.5 (50 MB of weights at 7.7
+// TB/s less the launch), 64 x 12288 x 4096 21.8 -> 11.9, 64 x 4096 x 4096 9.6
+// -> 6.4, 256 x 1024 x 1024 5.0 -> 4.1.  What bounds it then is the bytes a
+// CU loads, about 85 KB a microsecond (40 bytes a clock); loading the
+// fragments from memory to registers, 64-byte pieces of 16 rows, reached less
+// than half of that.
+constexpr int kThinWaves = 8;
+
+template <int TI, int TJ>
+struct ThinLds {
+  static constexpr int kStage = (TI + TJ) * 2048;  // one wave's operand stage
+  static constexpr int kPartial = TI * TJ * 1024;  // one wave's partial tile
+  static constexpr int kBytes = kThinWaves * (kStage > kPartial ? kStage : kPartial);
+};
+
+// The tile (tm, tn) of 16 TI x 16 TJ outputs; lds: ThinLds<TI, TJ>::kBytes.
+template <int PAIR, int TI, int TJ, int FMT>
+__device__ __forceinline__ void thin_tile(const GemmArgs& g, uint8_t* lds, int tm, int tn) {
+  constexpr bool kBlockScaled = PAIR == kPairBlock || PAIR == kPairBlockK || PAIR == kPairBlockE8;
+  constexpr bool kWeightBlocks = PAIR == kPairBlock || PAIR == kPairBlockE8;
+  static_assert(TJ <= 8 && 8 % TJ == 0, "a tile's columns lie in one 128-column weight block");
+  constexpr int W = kThinWaves, kColScales = kWeightBlocks ? 1 : TJ * 4;
+  const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+  const int row = lane & 15, grp = lane >> 4;
+  const int64_t m0 = (int64_t)tm * (TI * 16), n0 = (int64_t)tn * (TJ * 16);
+  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(g.sA, (uint32_t)(g.sa_count * 4));
+  const __amdgpu_buffer_rsrc_t rsB = make_rsrc(g.sB, (uint32_t)(g.sb_count * 4));
+  uint8_t* const stage = lds + wave * ThinLds<TI, TJ>::kStage;  // B's rows, then A's
+  const TileLoader<TI * 16, 1> ldA(g.A, g.lda, m0, g.M, 0);
+  const TileLoader<TJ * 16, 1> ldB(g.B, g.ldb, n0, g.N, 0);
+  const int kblocks = (int)(g.K / kBK);
+
+  // K block kb to the stage, its scales to registers.  Scale offsets of rows
+  // past M (columns past N) fall on other scales or past the array (zero):
+  // they only meet partials that are never stored.
+  float sa[TI], sb[kColScales];
+  auto issue = [&](int kb) {
+    if constexpr (kBlockScaled) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i) sa[i] = load_f32(rsA, ((int)m0 + i * 16 + row + kb * (int)g.sa_ld) * 4, 0);
+    }
+    if constexpr (kWeightBlocks) sb[0] = load_f32(rsB, ((int)(n0 / 128) * kblocks + kb) * 4, 0);
+    if constexpr (PAIR == kPairBlockK) {
+#pragma unroll
+      for (int q = 0; q < kColScales; ++q)
+        sb[q] = load_f32(rsB, ((int)n0 + (q / 4) * 16 + grp * 4 + q % 4 + kb * (int)g.sb_ld) * 4, 0);
+    }
+    ldB.load(kb * kBK, stage, 0);
+    ldA.load(kb * kBK, stage + TJ * 2048, 0);
+  };
+
+  v4f acc[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  // this lane's two chunks of a strip of 16 rows (see frag_addr)
+  const int sw = chunk_swizzle(row);
+  const int lo = row * 128 + (((2 * grp) ^ sw) << 4), hi = row * 128 + (((2 * grp + 1) ^ sw) << 4);
+  auto frag = [&](int strip) {
+    const v4u x = *reinterpret_cast<const v4u*>(stage + strip * 2048 + lo);
+    const v4u y = *reinterpret_cast<const v4u*>(stage + strip * 2048 + hi);
+    v8i f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      f[e] = (int)x[e];
+      f[4 + e] = (int)y[e];
+    }
+    return f;
+  };
+  if (wave < kblocks) issue(wave);
+  for (int kb = wave; kb < kblocks; kb += W) {
+    wait_vmem_all();  // this wave's stage and scales have landed
+    v8i af[TI], bf[TJ];
+    float ca[TI], cb[kColScales];
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) bf[j] = frag(j);
+#pragma unroll
+    for (int i = 0; i < TI; ++i) af[i] = frag(TJ + i);
+#pragma unroll
+    for (int i = 0; i < TI; ++i) ca[i] = sa[i];
+#pragma unroll
+    for (int q = 0; q < kColScales; ++q) cb[q] = sb[q];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read: the stage is free
+    if (kb + W < kblocks) issue(kb + W);
+    const v4f zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        if constexpr (PAIR == kPairBlockE8) {
+          acc[i][j] = mfma_16x16x128_e8(bf[j], af[i], acc[i][j], e8m0_of(cb[0]), e8m0_of(ca[i]));
+        } else if constexpr (!kBlockScaled) {
+          acc[i][j] = mfma_16x16x128<FMT>(bf[j], af[i], acc[i][j]);
+        } else {
+          const v4f p = mfma_16x16x128<FMT>(bf[j], af[i], zero);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if constexpr (PAIR == kPairBlock)
+              acc[i][j][r] = __builtin_fmaf(p[r], ca[i] * cb[0], acc[i][j][r]);
+            else
+              acc[i][j][r] = __builtin_fmaf(p[r] * ca[i], cb[j * 4 + r], acc[i][j][r]);
+          }
+        }
+      }
+  }
+
+  // the waves' partial tiles, over the stages (no load is in flight)
+  __syncthreads();
+  float4* const part = reinterpret_cast<float4*>(lds);
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+      part[(wave * TI * TJ + i * TJ + j) * 64 + lane] =
+          make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+  __syncthreads();
+  float st = 1.0f;
+  if (PAIR == kPairTensor) st = load_f32(rsA, 0, 0) * load_f32(rsB, 0, 0);
+  for (int e = threadIdx.x; e < TI * TJ * 64; e += W * 64) {
+    float4 v = part[e];
+#pragma unroll
+    for (int w = 1; w < W; ++w) {
+      const float4 q = part[w * TI * TJ * 64 + e];
+      v.x += q.x;
+      v.y += q.y;
+      v.z += q.z;
+      v.w += q.w;
+    }
+    const int l = e & 63, ij = e >> 6;
+    const int64_t m = m0 + (ij / TJ) * 16 + (l & 15), n = n0 + (ij % TJ) * 16 + (l >> 4) * 4;
+    if (m >= g.M || n >= g.N) continue;
+    float f[4] = {v.x, v.y, v.z, v.w};
+    if (PAIR == kPairTensor) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) f[r] = f[r] * st;
+    }
+    if (PAIR == kPairRow) {
+      const float sm = load_f32(rsA, (int)m * 4, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) f[r] = (f[r] * sm) * load_f32(rsB, (int)(n + r) * 4, 0);
+    }
+    const uint32_t w2[2] = {bf16x2_rne(f[0], f[1]), bf16x2_rne(f[2], f[3])};
+    uint16_t* const dst = g.C + m * g.ldc + n;
+    if (n + 4 <= g.N)
+      *reinterpret_cast<uint2*>(dst) = make_uint2(w2[0], w2[1]);
+    else
+      for (int x = 0; n + x < g.N; ++x) dst[x] = (uint16_t)(w2[x >> 1] >> (16 * (x & 1)));
+  }
+}
+
+template <int PAIR, int TI, int TJ, int FMT>
+__global__ __launch_bounds__(kThinWaves * 64) void gemm_thin_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[ThinLds<TI, TJ>::kBytes];
+  int tm, tn;
+  tile_coords<TI * 16, TJ * 16>(g.M, g.N, g.K, blockIdx.x, tm, tn);
+  thin_tile<PAIR, TI, TJ, FMT>(g, lds, tm, tn);
+}
+
 template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KS) void gemm_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[TileLds<PAIR, BM, BN, WM, WN, KS>::kBytes];
@@ -1160,6 +1329,14 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KS) void gemm_grouped_
   gemm_tile<PAIR, BM, BN, WM, WN, false, 0, KS>(*g, lds, tm, tn);
 }
 
+template <int PAIR, int TI, int TJ>
+__global__ __launch_bounds__(kThinWaves * 64) void gemm_grouped_thin_kernel(GemmGroup gs) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[ThinLds<TI, TJ>::kBytes];
+  int tm, tn;
+  const GemmArgs* g = grouped_at<TI * 16, TJ * 16>(gs, xcd_order(gs.tile_start[gs.count], blockIdx.x), tm, tn);
+  thin_tile<PAIR, TI, TJ, 0>(*g, lds, tm, tn);
+}
+
 template <int PAIR>
 __global__ __launch_bounds__(512) void gemm_grouped_large_kernel(GemmGroup gs, int full, int parts) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[LargeLds<PAIR>::kBytes];
@@ -1225,14 +1402,97 @@ inline bool k_groups(const GemmArgs& g) {
   return ((g.M + 63) / 64) * ((g.N + 63) / 64) <= 256 && (g.K / kBK) % 2 == 0;
 }
 
+// Thin tiles (16 TI x 16 TJ outputs, see thin_tile).
+enum { kThin16x16, kThin16x32, kThin32x32, kThin32x64, kThin64x64, kThinConfigs };
+constexpr int kThinM[kThinConfigs] = {16, 16, 32, 32, 64}, kThinN[kThinConfigs] = {16, 32, 32, 64, 64};
+
+// f(TI, TJ) of a thin tile, as integral constants.
+template <typename F>
+hipError_t with_thin(int config, F&& f) {
+  using std::integral_constant;
+  switch (config) {
+    case kThin16x16: return f(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+    case kThin16x32: return f(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+    case kThin32x32: return f(integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    case kThin32x64: return f(integral_constant<int, 2>{}, integral_constant<int, 4>{});
+    case kThin64x64: return f(integral_constant<int, 4>{}, integral_constant<int, 4>{});
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// Operand rows (of K bytes) that the busiest CU loads: its tiles times a
+// tile's rows of A (none past M) and of B.
+inline int64_t cu_rows(int64_t tiles, int64_t rows) { return (tiles + kCUs - 1) / kCUs * rows; }
+
+// The thin tile whose busiest CU loads the fewest rows, for the problems
+// M[i] x N[i] of one launch.  64 x 64, whose partial tiles take longest to
+// meet, from eight K blocks a wave on (256 x 12288 x 4096: 21.8 us against
+// 23.5 with two K groups; 64 x 4096 x 12288: 12.6 against 10.9).
+inline int thin_config(const GemmArgs* probs, int count, int64_t& rows) {
+  int best = 0;
+  for (int c = 0; c < kThinConfigs; ++c) {
+    if (c == kThin64x64 && probs[0].K < 8 * kThinWaves * kBK) continue;
+    int64_t tiles = 0, most = 0;
+    for (int i = 0; i < count; ++i) {
+      const GemmArgs& g = probs[i];
+      tiles += ((g.M + kThinM[c] - 1) / kThinM[c]) * ((g.N + kThinN[c] - 1) / kThinN[c]);
+      const int64_t per = (g.M < kThinM[c] ? g.M : kThinM[c]) + kThinN[c];
+      most = per > most ? per : most;
+    }
+    const int64_t r = cu_rows(tiles, most);
+    if (c == 0 || r < rows) {
+      best = c;
+      rows = r;
+    }
+  }
+  return best;
+}
+
+// Whether a problem too small for the 128 x 128 tiles of four waves is thin:
+// the tile kernels load fewer rows per CU only where they have tiles for most
+// of the CUs, and take longer per row: 1.13 times for 64 x 64 with two K
+// groups, 1.2 for 64 x 64 without (two workgroups per CU, which even out),
+// 1.33 for 128 x 128 with eight waves (measured: 75, 70 and 64 KB a
+// microsecond and CU against 85).  64 x 4096 x 12288 (192 tiles of 64 x 64)
+// stays: 10.9 us, thin 32 x 32 13.2; 128 x 4096 x 12288 (384 of 64 x 64):
+// 15.1, thin 19.2; 256 x 4096 x 12288 (192 of 128 x 128): 19.4, thin 26.9; 64
+// x 12288 x 4096 (64 tiles) 22.2 and 11.9.
+inline bool is_thin(const GemmArgs& g) {
+  const int64_t t64 = ((g.M + 63) / 64) * ((g.N + 63) / 64), mid = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+  const int64_t rows64 = (g.M < 64 ? g.M : 64) + 64;
+  int64_t tiled;  // in percent
+  if (k_groups(g))
+    tiled = cu_rows(t64, rows64) * 113;
+  else if (mid >= 128)
+    tiled = cu_rows(mid, (g.M < 128 ? g.M : 128) + 128) * 133;
+  else
+    tiled = t64 > kCUs ? t64 * rows64 * 120 / kCUs : rows64 * 120;
+  int64_t rows;
+  thin_config(&g, 1, rows);
+  return rows * 100 < tiled;
+}
+
+template <int PAIR, int FMT>
+hipError_t launch_thin(const GemmArgs& g, hipStream_t s) {
+  int64_t rows;
+  return with_thin(thin_config(&g, 1, rows), [&](auto ti, auto tj) {
+    constexpr int TI = decltype(ti)::value, TJ = decltype(tj)::value;
+    const int64_t tiles = ((g.M + TI * 16 - 1) / (TI * 16)) * ((g.N + TJ * 16 - 1) / (TJ * 16));
+    if (tiles <= 0 || tiles > 0x7fffffff) return hipErrorInvalidValue;
+    gemm_thin_kernel<PAIR, TI, TJ, FMT><<<dim3((unsigned)tiles), kThinWaves * 64, 0, s>>>(g);
+    return hipGetLastError();
+  });
+}
+
 // 256 x 256 tiles (8 waves of 128 x 64, see large_tiles) where they take less
 // time than 128 x 128 tiles (see takes_large); else 128 x 128 tiles (4 waves
-// of 64 x 64) when they fill the chip once; else, for skinny problems such as a decode step, whose time goes
-// into streaming the weights: 64 x 64 tiles with two K groups when those
+// of 64 x 64) when they fill the chip once; else, for skinny problems such as
+// a decode step, whose time goes into streaming the weights: thin tiles
+// (is_thin), 64 x 64 tiles with two K groups when those
 // fit (k_groups), 128 x 128 tiles of 8 waves of 32 x 64 with a four-stage
 // ring (one workgroup per CU) when there are 128 to 255 of them, and 64 x 64
-// tiles (4 waves of 32 x 32) below that.  Every choice but the K groups sums
-// an output's K blocks in the same order.  Quantized output needs whole
+// tiles (4 waves of 32 x 32) below that.  Every choice but the thin tiles and
+// the K groups sums an output's K blocks in the same order.  Quantized output needs whole
 // 128-column units in a tile: 256 or 128 tiles only.
 template <int PAIR, bool QOUT, int FMT>
 hipError_t launch_pair(const GemmArgs& g, hipStream_t s) {
@@ -1243,6 +1503,7 @@ hipError_t launch_pair(const GemmArgs& g, hipStream_t s) {
     return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
   } else {
     if (mid_tiles >= 256) return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
+    if (is_thin(g)) return launch_thin<PAIR, FMT>(g, s);
     if (k_groups(g)) return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT, 2>(g, s);
     if (mid_tiles >= 128) return launch_tiles<PAIR, 128, 128, 32, 64, QOUT, FMT>(g, s);
     return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT>(g, s);
@@ -1354,6 +1615,34 @@ FP8Q_GEMM_SPLITK(kPairRow)
 FP8Q_GEMM_SPLITK(kPairBlock)
 FP8Q_GEMM_SPLITK(kPairBlockK)
 #undef FP8Q_GEMM_SPLITK
+#define FP8Q_GEMM_THIN_TILES(PAIR, FMT)                               \
+  template __global__ void gemm_thin_kernel<PAIR, 1, 1, FMT>(GemmArgs); \
+  template __global__ void gemm_thin_kernel<PAIR, 1, 2, FMT>(GemmArgs); \
+  template __global__ void gemm_thin_kernel<PAIR, 2, 2, FMT>(GemmArgs); \
+  template __global__ void gemm_thin_kernel<PAIR, 2, 4, FMT>(GemmArgs); \
+  template __global__ void gemm_thin_kernel<PAIR, 4, 4, FMT>(GemmArgs);
+FP8Q_GEMM_THIN_TILES(kPairTensor, 0)
+FP8Q_GEMM_THIN_TILES(kPairRow, 0)
+FP8Q_GEMM_THIN_TILES(kPairBlockE8, 0)
+FP8Q_GEMM_THIN_TILES(kPairBlock, 0)
+FP8Q_GEMM_THIN_TILES(kPairBlock, 1)
+FP8Q_GEMM_THIN_TILES(kPairBlock, 2)
+FP8Q_GEMM_THIN_TILES(kPairBlock, 3)
+FP8Q_GEMM_THIN_TILES(kPairBlockK, 0)
+FP8Q_GEMM_THIN_TILES(kPairBlockK, 1)
+FP8Q_GEMM_THIN_TILES(kPairBlockK, 2)
+FP8Q_GEMM_THIN_TILES(kPairBlockK, 3)
+#undef FP8Q_GEMM_THIN_TILES
+#define FP8Q_GEMM_GROUPED_THIN(PAIR)                                    \
+  template __global__ void gemm_grouped_thin_kernel<PAIR, 1, 1>(GemmGroup); \
+  template __global__ void gemm_grouped_thin_kernel<PAIR, 1, 2>(GemmGroup); \
+  template __global__ void gemm_grouped_thin_kernel<PAIR, 2, 2>(GemmGroup); \
+  template __global__ void gemm_grouped_thin_kernel<PAIR, 2, 4>(GemmGroup); \
+  template __global__ void gemm_grouped_thin_kernel<PAIR, 4, 4>(GemmGroup);
+FP8Q_GEMM_GROUPED_THIN(kPairTensor)
+FP8Q_GEMM_GROUPED_THIN(kPairRow)
+FP8Q_GEMM_GROUPED_THIN(kPairBlock)
+#undef FP8Q_GEMM_GROUPED_THIN
 #define FP8Q_GEMM_LARGE(PAIR, QOUT, FMT) template __global__ void gemm_large_kernel<PAIR, QOUT, FMT>(GemmArgs, int, int);
 FP8Q_GEMM_LARGE(kPairTensor, false, 0)
 FP8Q_GEMM_LARGE(kPairRow, false, 0)
@@ -1402,6 +1691,18 @@ hipError_t launch_grouped_tiles(GemmGroup gs, hipStream_t s) {
 }
 
 template <int PAIR>
+hipError_t launch_grouped_thin(GemmGroup gs, hipStream_t s) {
+  int64_t rows;
+  return with_thin(thin_config(gs.prob, gs.count, rows), [&](auto ti, auto tj) {
+    constexpr int TI = decltype(ti)::value, TJ = decltype(tj)::value;
+    const int64_t total = count_tiles<TI * 16, TJ * 16>(gs);
+    if (total <= 0) return hipErrorInvalidValue;
+    gemm_grouped_thin_kernel<PAIR, TI, TJ><<<dim3((unsigned)total), kThinWaves * 64, 0, s>>>(gs);
+    return hipGetLastError();
+  });
+}
+
+template <int PAIR>
 hipError_t launch_grouped_large(GemmGroup gs, hipStream_t s) {
   const int64_t total = count_tiles<256, 256>(gs);
   if (total <= 0) return hipErrorInvalidValue;
@@ -1415,18 +1716,22 @@ hipError_t launch_grouped_large(GemmGroup gs, hipStream_t s) {
 // problem a single call would give one of them (the tile size from their
 // tile count over all, as launch_pair chooses it for one: for a skinny
 // problem among large ones that is a larger tile than its own, with the same
-// bits); the problems a single call would split into K groups (another
-// order of the K sum) go to a second launch.
+// bits); the problems a single call would give the thin tiles (which sum in
+// an order of their own, whatever their size) go to a second launch, and
+// those it would split into K groups to a third.
 template <int PAIR>
 hipError_t launch_grouped_pair(const GemmGroup& gs, hipStream_t s) {
-  GemmGroup tiled{}, thin{};
+  GemmGroup tiled{}, thin{}, grouped{};
   int64_t big = 0, mid = 0;
   for (int i = 0; i < gs.count; ++i) {
     const GemmArgs& g = gs.prob[i];
     const int64_t big_i = ((g.M + 255) / 256) * ((g.N + 255) / 256);
     const int64_t mid_i = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-    if (!takes_large(big_i, mid_i) && mid_i < 256 && k_groups(g)) {
+    const bool skinny = !takes_large(big_i, mid_i) && mid_i < 256;
+    if (skinny && is_thin(g)) {
       thin.prob[thin.count++] = g;
+    } else if (skinny && k_groups(g)) {
+      grouped.prob[grouped.count++] = g;
     } else {
       tiled.prob[tiled.count++] = g;
       big += big_i;
@@ -1439,7 +1744,11 @@ hipError_t launch_grouped_pair(const GemmGroup& gs, hipStream_t s) {
                                                : launch_grouped_tiles<PAIR, 64, 64, 32, 32>(tiled, s);
     if (e != hipSuccess) return e;
   }
-  if (thin.count) return launch_grouped_tiles<PAIR, 64, 64, 32, 32, 2>(thin, s);
+  if (thin.count) {
+    const hipError_t e = launch_grouped_thin<PAIR>(thin, s);
+    if (e != hipSuccess) return e;
+  }
+  if (grouped.count) return launch_grouped_tiles<PAIR, 64, 64, 32, 32, 2>(grouped, s);
   return hipSuccess;
 }
 
@@ -1492,20 +1801,33 @@ hipError_t launch_gemm_quantized(const GemmArgs& g, int pair, hipStream_t s) {
   return launch_split<kPairBlock, true, 0>(g, s);
 }
 
+template <int PAIR>
+hipError_t launch_splitk_pair(const GemmArgs& g, unsigned grid, hipStream_t s) {
+  // Thin tiles where they take less time: a split loads 256 K / S bytes per
+  // CU and then pays about 10 us (900 KB of loads) for the partial tiles'
+  // way through memory; the thin tiles' waves meet in LDS.  256 x 12288 x
+  // 4096: split over four 24.9 us, thin 64 x 64 tiles 21.9; 256 x 25600 x
+  // 5120 stays split.
+  int64_t rows;
+  thin_config(&g, 1, rows);
+  if (rows * g.K < 256 * g.K / g.splits + 900000) return launch_thin<PAIR, 0>(g, s);
+  gemm_splitk_kernel<PAIR, 128, 128, 32, 64, 0><<<dim3(grid), 512, 0, s>>>(g);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_splitk(const GemmArgs& g, int pair, hipStream_t s) {
   if (g.splits <= 1) return launch_gemm(g, pair, 0, s);
   const int64_t tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
   if (!g.part || !g.cnt || g.splits > 8 || (g.K / kBK) % g.splits || tiles * g.splits > 256)
     return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(tiles * g.splits));
+  const unsigned grid = (unsigned)(tiles * g.splits);
   switch (pair) {
-    case kPairTensor: gemm_splitk_kernel<kPairTensor, 128, 128, 32, 64, 0><<<grid, 512, 0, s>>>(g); break;
-    case kPairRow: gemm_splitk_kernel<kPairRow, 128, 128, 32, 64, 0><<<grid, 512, 0, s>>>(g); break;
-    case kPairBlock: gemm_splitk_kernel<kPairBlock, 128, 128, 32, 64, 0><<<grid, 512, 0, s>>>(g); break;
-    case kPairBlockK: gemm_splitk_kernel<kPairBlockK, 128, 128, 32, 64, 0><<<grid, 512, 0, s>>>(g); break;
+    case kPairTensor: return launch_splitk_pair<kPairTensor>(g, grid, s);
+    case kPairRow: return launch_splitk_pair<kPairRow>(g, grid, s);
+    case kPairBlock: return launch_splitk_pair<kPairBlock>(g, grid, s);
+    case kPairBlockK: return launch_splitk_pair<kPairBlockK>(g, grid, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace fp8q
