@@ -1086,7 +1086,8 @@ struct ThinLds {
 };
 
 // The tile (tm, tn) of 16 TI x 16 TJ outputs; lds: ThinLds<TI, TJ>::kBytes.
-template <int PAIR, int TI, int TJ, int FMT>
+// QOUT: quantized output, with tiles of 32 x 128 (whole units).
+template <int PAIR, int TI, int TJ, bool QOUT, int FMT>
 __device__ __forceinline__ void thin_tile(const GemmArgs& g, uint8_t* lds, int tm, int tn) {
   constexpr bool kBlockScaled = PAIR == kPairBlock || PAIR == kPairBlockK || PAIR == kPairBlockE8;
   constexpr bool kWeightBlocks = PAIR == kPairBlock || PAIR == kPairBlockE8;
@@ -1189,7 +1190,7 @@ __device__ __forceinline__ void thin_tile(const GemmArgs& g, uint8_t* lds, int t
   __syncthreads();
   float st = 1.0f;
   if (PAIR == kPairTensor) st = load_f32(rsA, 0, 0) * load_f32(rsB, 0, 0);
-  for (int e = threadIdx.x; e < TI * TJ * 64; e += W * 64) {
+  auto sum_of = [&](int e) {
     float4 v = part[e];
 #pragma unroll
     for (int w = 1; w < W; ++w) {
@@ -1199,6 +1200,32 @@ __device__ __forceinline__ void thin_tile(const GemmArgs& g, uint8_t* lds, int t
       v.z += q.z;
       v.w += q.w;
     }
+    return v;
+  };
+  if constexpr (QOUT) {
+    // the bf16 tile to LDS (over the partials, once all are read), 256-byte
+    // rows with chunk c at c ^ (row & 15), as store_quantized reads it
+    static_assert(TI * 16 == W * 4 && TJ == 8, "one pass of 16 threads per row and unit");
+    constexpr int kItems = TI * TJ / W;
+    uint2 packed[kItems];
+#pragma unroll
+    for (int x = 0; x < kItems; ++x) {
+      const float4 v = sum_of(threadIdx.x + x * W * 64);
+      packed[x] = make_uint2(bf16x2_rne(v.x, v.y), bf16x2_rne(v.z, v.w));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < kItems; ++x) {
+      const int e = threadIdx.x + x * W * 64, l = e & 63, ij = e >> 6;
+      const int mt = (ij / TJ) * 16 + (l & 15), nt = (ij % TJ) * 16 + (l >> 4) * 4;
+      *reinterpret_cast<uint2*>(lds + mt * 256 + (((nt >> 3) ^ (mt & 15)) << 4) + ((nt >> 2) & 1) * 8) = packed[x];
+    }
+    __syncthreads();
+    store_quantized<1, 256, 15, W * 4>(g, lds, m0, n0, 16);
+    return;
+  }
+  for (int e = threadIdx.x; e < TI * TJ * 64; e += W * 64) {
+    const float4 v = sum_of(e);
     const int l = e & 63, ij = e >> 6;
     const int64_t m = m0 + (ij / TJ) * 16 + (l & 15), n = n0 + (ij % TJ) * 16 + (l >> 4) * 4;
     if (m >= g.M || n >= g.N) continue;
@@ -1221,12 +1248,12 @@ __device__ __forceinline__ void thin_tile(const GemmArgs& g, uint8_t* lds, int t
   }
 }
 
-template <int PAIR, int TI, int TJ, int FMT>
+template <int PAIR, int TI, int TJ, bool QOUT, int FMT>
 __global__ __launch_bounds__(kThinWaves * 64) void gemm_thin_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[ThinLds<TI, TJ>::kBytes];
   int tm, tn;
   tile_coords<TI * 16, TJ * 16>(g.M, g.N, g.K, blockIdx.x, tm, tn);
-  thin_tile<PAIR, TI, TJ, FMT>(g, lds, tm, tn);
+  thin_tile<PAIR, TI, TJ, QOUT, FMT>(g, lds, tm, tn);
 }
 
 template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1>
@@ -1334,7 +1361,7 @@ __global__ __launch_bounds__(kThinWaves * 64) void gemm_grouped_thin_kernel(Gemm
   __shared__ __attribute__((aligned(1024))) uint8_t lds[ThinLds<TI, TJ>::kBytes];
   int tm, tn;
   const GemmArgs* g = grouped_at<TI * 16, TJ * 16>(gs, xcd_order(gs.tile_start[gs.count], blockIdx.x), tm, tn);
-  thin_tile<PAIR, TI, TJ, 0>(*g, lds, tm, tn);
+  thin_tile<PAIR, TI, TJ, false, 0>(*g, lds, tm, tn);
 }
 
 template <int PAIR>
@@ -1472,38 +1499,46 @@ inline bool is_thin(const GemmArgs& g) {
   return rows * 100 < tiled;
 }
 
-template <int PAIR, int FMT>
+template <int PAIR, bool QOUT, int FMT>
 hipError_t launch_thin(const GemmArgs& g, hipStream_t s) {
-  int64_t rows;
-  return with_thin(thin_config(&g, 1, rows), [&](auto ti, auto tj) {
+  auto launch = [&](auto ti, auto tj) {
     constexpr int TI = decltype(ti)::value, TJ = decltype(tj)::value;
     const int64_t tiles = ((g.M + TI * 16 - 1) / (TI * 16)) * ((g.N + TJ * 16 - 1) / (TJ * 16));
     if (tiles <= 0 || tiles > 0x7fffffff) return hipErrorInvalidValue;
-    gemm_thin_kernel<PAIR, TI, TJ, FMT><<<dim3((unsigned)tiles), kThinWaves * 64, 0, s>>>(g);
+    gemm_thin_kernel<PAIR, TI, TJ, QOUT, FMT><<<dim3((unsigned)tiles), kThinWaves * 64, 0, s>>>(g);
     return hipGetLastError();
-  });
+  };
+  if constexpr (QOUT) {
+    return launch(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+  } else {
+    int64_t rows;
+    return with_thin(thin_config(&g, 1, rows), launch);
+  }
 }
 
 // 256 x 256 tiles (8 waves of 128 x 64, see large_tiles) where they take less
 // time than 128 x 128 tiles (see takes_large); else 128 x 128 tiles (4 waves
-// of 64 x 64) when they fill the chip once; else, for skinny problems such as
-// a decode step, whose time goes into streaming the weights: thin tiles
-// (is_thin), 64 x 64 tiles with two K groups when those
-// fit (k_groups), 128 x 128 tiles of 8 waves of 32 x 64 with a four-stage
-// ring (one workgroup per CU) when there are 128 to 255 of them, and 64 x 64
+// of 64 x 64, two workgroups per CU) when there are more than one per CU;
+// else, for skinny problems such as a decode step, whose time goes into
+// streaming the weights: thin tiles (is_thin), 64 x 64 tiles with two K groups
+// when those fit (k_groups), 128 x 128 tiles of 8 waves of 32 x 64 with a
+// four-stage ring (one workgroup per CU) when there are 128 to 256 of them
+// (1024 x 4096 x 4096, 256 tiles: 22.2 us, with 4 waves 24.6), and 64 x 64
 // tiles (4 waves of 32 x 32) below that.  Every choice but the thin tiles and
-// the K groups sums an output's K blocks in the same order.  Quantized output needs whole
-// 128-column units in a tile: 256 or 128 tiles only.
+// the K groups sums an output's K blocks in the same order.  Quantized output
+// needs whole 128-column units in a tile: 256 or 128 tiles, or thin tiles of
+// 32 x 128 where fp8q_gemm takes thin tiles, whose sums it must repeat (64 x
+// 4096 x 4096, 32 tiles of 128 x 128: 24.8 us, thin 10.9).
 template <int PAIR, bool QOUT, int FMT>
 hipError_t launch_pair(const GemmArgs& g, hipStream_t s) {
   const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
   const int64_t mid_tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
   if (takes_large(big_tiles, mid_tiles)) return launch_large<PAIR, QOUT, FMT>(g, s);
+  if (mid_tiles > kCUs) return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
+  if (is_thin(g)) return launch_thin<PAIR, QOUT, FMT>(g, s);
   if constexpr (QOUT) {
-    return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
+    return launch_tiles<PAIR, 128, 128, 32, 64, QOUT, FMT>(g, s);
   } else {
-    if (mid_tiles >= 256) return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
-    if (is_thin(g)) return launch_thin<PAIR, FMT>(g, s);
     if (k_groups(g)) return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT, 2>(g, s);
     if (mid_tiles >= 128) return launch_tiles<PAIR, 128, 128, 32, 64, QOUT, FMT>(g, s);
     return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT>(g, s);
@@ -1615,12 +1650,12 @@ FP8Q_GEMM_SPLITK(kPairRow)
 FP8Q_GEMM_SPLITK(kPairBlock)
 FP8Q_GEMM_SPLITK(kPairBlockK)
 #undef FP8Q_GEMM_SPLITK
-#define FP8Q_GEMM_THIN_TILES(PAIR, FMT)                               \
-  template __global__ void gemm_thin_kernel<PAIR, 1, 1, FMT>(GemmArgs); \
-  template __global__ void gemm_thin_kernel<PAIR, 1, 2, FMT>(GemmArgs); \
-  template __global__ void gemm_thin_kernel<PAIR, 2, 2, FMT>(GemmArgs); \
-  template __global__ void gemm_thin_kernel<PAIR, 2, 4, FMT>(GemmArgs); \
-  template __global__ void gemm_thin_kernel<PAIR, 4, 4, FMT>(GemmArgs);
+#define FP8Q_GEMM_THIN_TILES(PAIR, FMT)                                       \
+  template __global__ void gemm_thin_kernel<PAIR, 1, 1, false, FMT>(GemmArgs); \
+  template __global__ void gemm_thin_kernel<PAIR, 1, 2, false, FMT>(GemmArgs); \
+  template __global__ void gemm_thin_kernel<PAIR, 2, 2, false, FMT>(GemmArgs); \
+  template __global__ void gemm_thin_kernel<PAIR, 2, 4, false, FMT>(GemmArgs); \
+  template __global__ void gemm_thin_kernel<PAIR, 4, 4, false, FMT>(GemmArgs);
 FP8Q_GEMM_THIN_TILES(kPairTensor, 0)
 FP8Q_GEMM_THIN_TILES(kPairRow, 0)
 FP8Q_GEMM_THIN_TILES(kPairBlockE8, 0)
@@ -1633,6 +1668,7 @@ FP8Q_GEMM_THIN_TILES(kPairBlockK, 1)
 FP8Q_GEMM_THIN_TILES(kPairBlockK, 2)
 FP8Q_GEMM_THIN_TILES(kPairBlockK, 3)
 #undef FP8Q_GEMM_THIN_TILES
+template __global__ void gemm_thin_kernel<kPairBlock, 2, 8, true, 0>(GemmArgs);
 #define FP8Q_GEMM_GROUPED_THIN(PAIR)                                    \
   template __global__ void gemm_grouped_thin_kernel<PAIR, 1, 1>(GemmGroup); \
   template __global__ void gemm_grouped_thin_kernel<PAIR, 1, 2>(GemmGroup); \
@@ -1658,6 +1694,7 @@ FP8Q_GEMM_LARGE(kPairBlockK, false, 2)
 FP8Q_GEMM_LARGE(kPairBlockK, false, 3)
 #undef FP8Q_GEMM_LARGE
 template __global__ void gemm_kernel<kPairBlock, 128, 128, 64, 64, true, 0>(GemmArgs);
+template __global__ void gemm_kernel<kPairBlock, 128, 128, 32, 64, true, 0>(GemmArgs);
 #define FP8Q_GEMM_GROUPED(PAIR)                                                     \
   template __global__ void gemm_grouped_large_kernel<PAIR>(GemmGroup, int, int);       \
   template __global__ void gemm_grouped_kernel<PAIR, 128, 128, 64, 64>(GemmGroup);     \
@@ -1727,7 +1764,7 @@ hipError_t launch_grouped_pair(const GemmGroup& gs, hipStream_t s) {
     const GemmArgs& g = gs.prob[i];
     const int64_t big_i = ((g.M + 255) / 256) * ((g.N + 255) / 256);
     const int64_t mid_i = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-    const bool skinny = !takes_large(big_i, mid_i) && mid_i < 256;
+    const bool skinny = !takes_large(big_i, mid_i) && mid_i <= kCUs;
     if (skinny && is_thin(g)) {
       thin.prob[thin.count++] = g;
     } else if (skinny && k_groups(g)) {
@@ -1810,7 +1847,7 @@ hipError_t launch_splitk_pair(const GemmArgs& g, unsigned grid, hipStream_t s) {
   // 5120 stays split.
   int64_t rows;
   thin_config(&g, 1, rows);
-  if (rows * g.K < 256 * g.K / g.splits + 900000) return launch_thin<PAIR, 0>(g, s);
+  if (rows * g.K < 256 * g.K / g.splits + 900000) return launch_thin<PAIR, false, 0>(g, s);
   gemm_splitk_kernel<PAIR, 128, 128, 32, 64, 0><<<dim3(grid), 512, 0, s>>>(g);
   return hipGetLastError();
 }

@@ -22,8 +22,8 @@ pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
 B1, B128 = fp8q.BLOCK_1x128, fp8q.BLOCK_128x128
-# (M, K, N): 16 x 16, 16 x 16 with one K block, 16 x 32, 32 x 32 (odd blocks), 32 x 64, 64 x 64
-SHAPES = [(1, 1152, 512), (13, 128, 384), (30, 1024, 4096), (61, 1920, 4096), (121, 1024, 4096), (250, 2304, 4096)]
+# (M, K, N): 16 x 16, 16 x 16 with one K block, 16 x 32, 32 x 32 (odd blocks), 32 x 64, 64 x 64 (K from 8192 on)
+SHAPES = [(1, 1152, 512), (13, 128, 384), (30, 1024, 4096), (61, 1920, 4096), (121, 1024, 4096), (250, 8320, 4096)]
 
 
 @pytest.mark.parametrize("pair", list(PAIRS))
@@ -35,7 +35,8 @@ def test_thin_against_oracle(pair, shape):
         N -= 6                                   # ragged columns where the pair allows them
     a = synth.activations(M, K, seed=801, outlier_seed=802, device=DEV)
     b = synth.weights(N, K, seed=803, device=DEV)
-    run_pair(a, b, ga, gb, label="thin %s" % pair, pad=-N % 4 or 4)
+    run_pair(a, b, ga, gb, rows=np.unique(np.append(np.arange(0, M, 1 + M // 40), M - 1)), label="thin %s" % pair,
+             pad=-N % 4 or 4)
 
 
 @pytest.mark.parametrize("shape", SHAPES)
@@ -66,6 +67,20 @@ def test_thin_pow2_and_formats(shape):
             x = (e5 if fmt & 1 else e4)[:M]
             y = (e5 if fmt & 2 else e4)[M:]
             assert torch.equal(fp8q.gemm_formats(x, sa, B1, y, sb, gb, fmt), want), (pair, fmt)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_thin_quantized_output(shape):
+    """The quantized output is the quantizer's on the plain call's output,
+    bit for bit (both sum in the thin tiles' order)."""
+    M, K, N = shape
+    A, sA = fp8q.quantize(synth.activations(M, K, seed=841, outlier_seed=842, device=DEV), B1)
+    B, sB = fp8q.quantize(synth.weights(N, K, seed=843, device=DEV), B128)
+    codes = torch.full((M, N + 128), 0x55, dtype=torch.uint8, device=DEV)
+    _, scales = fp8q.gemm_quantized(A, sA, B1, B, sB, B128, codes=codes[:, :N])
+    want, ws = fp8q.quantize(fp8q.gemm(A, sA, B1, B, sB, B128), B1)
+    assert torch.equal(codes[:, :N], want) and torch.equal(scales, ws)
+    assert torch.all(codes[:, N:] == 0x55), "columns past N were written"
 
 
 @pytest.mark.parametrize("M,K", [(8, 2048), (40, 384), (100, 1024)])
