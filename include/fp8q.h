@@ -277,7 +277,9 @@ int64_t fp8q_gemm_splitk_workspace(int64_t M, int64_t N, int64_t K);
  * (fewer than 128).  The K blocks of each tile are split over S workgroups (S a power
  * of two up to 8, S x tiles <= 256, at least four K blocks each), so that
  * each CU streams 1/S of the tile's operand rows; the S fp32 partial tiles
- * are added in a fixed order, then rounded to bf16 once.  The product,
+ * are added in a fixed order, then rounded to bf16 once.  Where small tiles
+ * whose waves split K inside one workgroup take less time, they run instead
+ * (the workspace rules stay those of the split).  The product,
  * pairs, layouts, shape and alignment rules are those of fp8q_gemm, and
  * the result is the same on every run; its K sum is grouped differently
  * from fp8q_gemm's, so the last bits of an output can differ.  Problems
