@@ -338,6 +338,53 @@ __global__ __launch_bounds__(kThreads) void quant_tile_kernel(QuantArgs a) {
   }
 }
 
+// 1x128 units, plain layout, up to kFewTiles tiles of 32 x 512: a thread
+// takes two rows instead of eight, so that there are four times the waves and
+// each encodes 16 elements, not 64, between its loads and its stores.  A
+// workgroup covers 8 rows x 512 columns, wave w rows 2w and 2w + 1.  Every
+// lane forms its unit's S and 1/S itself (eight rows shared them by shuffles).
+// Back to back, eight rows and two: 256 x 12288 3.98 -> 3.58 us, 2048 x 4096
+// 7.37 -> 6.44, 3001 x 5120 10.98 -> 9.55, 8192 x 4096 19.98 -> 18.64, 16384 x
+// 4096 37.4 -> 35.7 (5.6 TB/s; a copy reaches 5.2).  The line is the largest
+// size measured; past it, where the kernel is one long stream either way, and
+// where rows / 8 could pass the grid's limit, the eight-row kernel stays.
+constexpr int kFewRows = 2;
+constexpr int64_t kFewTiles = 4096;
+
+template <bool E5>
+__global__ __launch_bounds__(kThreads) void quant_few_kernel(QuantArgs a) {
+  const int64_t row0 = ((int64_t)blockIdx.y * (kThreads / 64) + (threadIdx.x >> 6)) * kFewRows;
+  const int64_t c = (int64_t)blockIdx.x * kWideCols + (threadIdx.x & 63) * 8;
+  uint4 w[kFewRows];
+#pragma unroll
+  for (int i = 0; i < kFewRows; ++i) {
+    w[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (c < a.cols && row0 + i < a.rows) w[i] = *reinterpret_cast<const uint4*>(a.x + (row0 + i) * a.ldx + c);
+  }
+#pragma unroll
+  for (int i = 0; i < kFewRows; ++i) {
+    const uint32_t v[4] = {w[i].x, w[i].y, w[i].z, w[i].w};
+    float m = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m = fmaxf(m, fmaxf(fabsf(bf16_lo(v[e])), fabsf(bf16_hi(v[e]))));
+    const UnitScale u = unit_scale_fmt<E5>(row16_max(m), a.pow2 != 0);
+    float q[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float lo = bf16_lo(v[e]), hi = bf16_hi(v[e]);
+      q[2 * e] = u.fast ? fast_quotient(lo, u.s, u.r) : slow_quotient(lo, u.s, u.r);
+      q[2 * e + 1] = u.fast ? fast_quotient(hi, u.s, u.r) : slow_quotient(hi, u.s, u.r);
+    }
+    const int64_t r = row0 + i;
+    if (c < a.cols && r < a.rows) {
+      const uint32_t c0 = fp8_pack2<E5, true>(q[2], q[3], fp8_pack2<E5, false>(q[0], q[1], 0u));
+      const uint32_t c1 = fp8_pack2<E5, true>(q[6], q[7], fp8_pack2<E5, false>(q[4], q[5], 0u));
+      *reinterpret_cast<uint2*>(a.codes + r * a.ldc + c) = make_uint2(c0, c1);
+      if ((threadIdx.x & 15) == 0) a.scales[(c >> 7) * a.rows + r] = u.s;
+    }
+  }
+}
+
 // Both operand layouts of the backward pass from one read.  A 128 x 128
 // tile is quantized twice: per 1x128 unit (its rows), with codes stored as
 // read and scales at (c / 128) * rows + r, and per 128x1 unit (its
@@ -674,7 +721,14 @@ template <bool E5>
 hipError_t launch_quantize_fmt(const QuantArgs& a, int granularity, bool trans, int64_t nscales, hipStream_t s) {
   (void)nscales;
   switch (granularity) {
-    case 3: return trans ? launch_tile<kBlock1x128, true, E5>(a, s) : launch_tile<kBlock1x128, false, E5>(a, s);
+    case 3:
+      if (!trans && ((a.cols + kWideCols - 1) / kWideCols) * ((a.rows + kWideRows - 1) / kWideRows) <= kFewTiles) {
+        constexpr int64_t rows = kThreads / 64 * kFewRows;
+        const dim3 grid((unsigned)((a.cols + kWideCols - 1) / kWideCols), (unsigned)((a.rows + rows - 1) / rows));
+        quant_few_kernel<E5><<<grid, kThreads, 0, s>>>(a);
+        return hipGetLastError();
+      }
+      return trans ? launch_tile<kBlock1x128, true, E5>(a, s) : launch_tile<kBlock1x128, false, E5>(a, s);
     case 4: return trans ? launch_tile<kBlock128x1, true, E5>(a, s) : launch_tile<kBlock128x1, false, E5>(a, s);
     case 5:
       return trans ? launch_tile<kBlock128x128, true, E5>(a, s) : launch_tile<kBlock128x128, false, E5>(a, s);
