@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "dispatch.h"
 #include "internal.h"
 
 namespace fp8q {
@@ -1276,7 +1277,6 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KS) void gemm_kernel(G
 // 4.25 rounds, 321 -> 301 us; 2048 x 4096 x 12288, 1.5 rounds, 105 us on 128
 // x 128 tiles -> 95 us).  Every tile shape sums an output's K blocks in the
 // same order, so the cut changes no bit.
-constexpr int kCUs = 256;
 
 template <int PAIR>
 struct LargeLds {
@@ -1381,36 +1381,6 @@ hipError_t launch_tiles(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The grid of a large launch of `total` 256 x 256 tiles: `full` whole tiles,
-// then the rest in `parts` (see large_tiles).  The last round is cut when its
-// parts fit in one round of the CUs: up to a quarter of them in four, up to
-// half in two; a fuller last round keeps whole tiles.
-struct LargePlan {
-  int full, parts, grid, cost;
-};
-inline LargePlan large_plan(int64_t total) {
-  const int rest = (int)(total % kCUs), rounds = (int)(total / kCUs);
-  LargePlan p;
-  p.parts = rest == 0 || rest > kCUs / 2 ? 1 : (rest <= kCUs / 4 ? 4 : 2);
-  p.full = p.parts == 1 ? (int)total : rounds * kCUs;
-  p.grid = p.full + (p.parts == 1 ? 0 : rest * p.parts);
-  p.cost = 100 * rounds + (rest == 0 ? 0 : p.parts == 4 ? 40 : p.parts == 2 ? 62 : 90);
-  return p;
-}
-
-// Whether `big` 256 x 256 tiles run before `mid` 128 x 128 tiles (the same
-// outputs) would: both in percent of a whole 256 x 256 tile's time.  512 of
-// the 128 x 128 tiles (four waves, two workgroups per CU) take 59, up to 256
-// (one per CU) 37; a last round of whole 256 x 256 tiles on part of the chip
-// 90 (measured at K = 4096: 192 tiles 47 us, 256 tiles 56 us, 512 of 128 x
-// 128 33 us, 256 of them 20.6 us).
-inline bool takes_large(int64_t big, int64_t mid) {
-  if (big > 0x3fffffff / 100) return true;
-  const int64_t rest = mid % (2 * kCUs);
-  const int64_t cost_mid = 59 * (mid / (2 * kCUs)) + (rest == 0 ? 0 : rest <= kCUs ? 37 : 59);
-  return large_plan(big).cost < cost_mid;
-}
-
 template <int PAIR, bool QOUT, int FMT>
 hipError_t launch_large(const GemmArgs& g, hipStream_t s) {
   const int64_t tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
@@ -1419,19 +1389,6 @@ hipError_t launch_large(const GemmArgs& g, hipStream_t s) {
   gemm_large_kernel<PAIR, QOUT, FMT><<<dim3((unsigned)p.grid), 512, 0, s>>>(g, p.full, p.parts);
   return hipGetLastError();
 }
-
-// Two K groups per 64 x 64 tile (one workgroup of 8 waves per CU) when there
-// are at most 256 such tiles, so that a CU would hold one workgroup anyway,
-// and the K blocks split evenly; more tiles keep two 4-wave workgroups per
-// CU (measured: 256 x 12288 x 4096 35 -> 28 us with groups, 256 x 4096 x
-// 12288 with its 768 tiles 31 -> 34 us).
-inline bool k_groups(const GemmArgs& g) {
-  return ((g.M + 63) / 64) * ((g.N + 63) / 64) <= 256 && (g.K / kBK) % 2 == 0;
-}
-
-// Thin tiles (16 TI x 16 TJ outputs, see thin_tile).
-enum { kThin16x16, kThin16x32, kThin32x32, kThin32x64, kThin64x64, kThinConfigs };
-constexpr int kThinM[kThinConfigs] = {16, 16, 32, 32, 64}, kThinN[kThinConfigs] = {16, 32, 32, 64, 64};
 
 // f(TI, TJ) of a thin tile, as integral constants.
 template <typename F>
@@ -1447,57 +1404,7 @@ hipError_t with_thin(int config, F&& f) {
   }
 }
 
-// Operand rows (of K bytes) that the busiest CU loads: its tiles times a
-// tile's rows of A (none past M) and of B.
-inline int64_t cu_rows(int64_t tiles, int64_t rows) { return (tiles + kCUs - 1) / kCUs * rows; }
-
-// The thin tile whose busiest CU loads the fewest rows, for the problems
-// M[i] x N[i] of one launch.  64 x 64, whose partial tiles take longest to
-// meet, from eight K blocks a wave on (256 x 12288 x 4096: 21.8 us against
-// 23.5 with two K groups; 64 x 4096 x 12288: 12.6 against 10.9).
-inline int thin_config(const GemmArgs* probs, int count, int64_t& rows) {
-  int best = 0;
-  for (int c = 0; c < kThinConfigs; ++c) {
-    if (c == kThin64x64 && probs[0].K < 8 * kThinWaves * kBK) continue;
-    int64_t tiles = 0, most = 0;
-    for (int i = 0; i < count; ++i) {
-      const GemmArgs& g = probs[i];
-      tiles += ((g.M + kThinM[c] - 1) / kThinM[c]) * ((g.N + kThinN[c] - 1) / kThinN[c]);
-      const int64_t per = (g.M < kThinM[c] ? g.M : kThinM[c]) + kThinN[c];
-      most = per > most ? per : most;
-    }
-    const int64_t r = cu_rows(tiles, most);
-    if (c == 0 || r < rows) {
-      best = c;
-      rows = r;
-    }
-  }
-  return best;
-}
-
-// Whether a problem too small for the 128 x 128 tiles of four waves is thin:
-// the tile kernels load fewer rows per CU only where they have tiles for most
-// of the CUs, and take longer per row: 1.13 times for 64 x 64 with two K
-// groups, 1.2 for 64 x 64 without (two workgroups per CU, which even out),
-// 1.33 for 128 x 128 with eight waves (measured: 75, 70 and 64 KB a
-// microsecond and CU against 85).  64 x 4096 x 12288 (192 tiles of 64 x 64)
-// stays: 10.9 us, thin 32 x 32 13.2; 128 x 4096 x 12288 (384 of 64 x 64):
-// 15.1, thin 19.2; 256 x 4096 x 12288 (192 of 128 x 128): 19.4, thin 26.9; 64
-// x 12288 x 4096 (64 tiles) 22.2 and 11.9.
-inline bool is_thin(const GemmArgs& g) {
-  const int64_t t64 = ((g.M + 63) / 64) * ((g.N + 63) / 64), mid = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-  const int64_t rows64 = (g.M < 64 ? g.M : 64) + 64;
-  int64_t tiled;  // in percent
-  if (k_groups(g))
-    tiled = cu_rows(t64, rows64) * 113;
-  else if (mid >= 128)
-    tiled = cu_rows(mid, (g.M < 128 ? g.M : 128) + 128) * 133;
-  else
-    tiled = t64 > kCUs ? t64 * rows64 * 120 / kCUs : rows64 * 120;
-  int64_t rows;
-  thin_config(&g, 1, rows);
-  return rows * 100 < tiled;
-}
+inline GemmSize size_of(const GemmArgs& g) { return GemmSize{g.M, g.N, g.K}; }
 
 template <int PAIR, bool QOUT, int FMT>
 hipError_t launch_thin(const GemmArgs& g, hipStream_t s) {
@@ -1511,38 +1418,27 @@ hipError_t launch_thin(const GemmArgs& g, hipStream_t s) {
   if constexpr (QOUT) {
     return launch(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
   } else {
+    const GemmSize size = size_of(g);
     int64_t rows;
-    return with_thin(thin_config(&g, 1, rows), launch);
+    return with_thin(thin_config(&size, 1, rows), launch);
   }
 }
 
-// 256 x 256 tiles (8 waves of 128 x 64, see large_tiles) where they take less
-// time than 128 x 128 tiles (see takes_large); else 128 x 128 tiles (4 waves
-// of 64 x 64, two workgroups per CU) when there are more than one per CU;
-// else, for skinny problems such as a decode step, whose time goes into
-// streaming the weights: thin tiles (is_thin), 64 x 64 tiles with two K groups
-// when those fit (k_groups), 128 x 128 tiles of 8 waves of 32 x 64 with a
-// four-stage ring (one workgroup per CU) when there are 128 to 256 of them
-// (1024 x 4096 x 4096, 256 tiles: 22.2 us, with 4 waves 24.6), and 64 x 64
-// tiles (4 waves of 32 x 32) below that.  Every choice but the thin tiles and
-// the K groups sums an output's K blocks in the same order.  Quantized output
-// needs whole 128-column units in a tile: 256 or 128 tiles, or thin tiles of
-// 32 x 128 where fp8q_gemm takes thin tiles, whose sums it must repeat (64 x
-// 4096 x 4096, 32 tiles of 128 x 128: 24.8 us, thin 10.9).
 template <int PAIR, bool QOUT, int FMT>
 hipError_t launch_pair(const GemmArgs& g, hipStream_t s) {
-  const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-  const int64_t mid_tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-  if (takes_large(big_tiles, mid_tiles)) return launch_large<PAIR, QOUT, FMT>(g, s);
-  if (mid_tiles > kCUs) return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
-  if (is_thin(g)) return launch_thin<PAIR, QOUT, FMT>(g, s);
-  if constexpr (QOUT) {
-    return launch_tiles<PAIR, 128, 128, 32, 64, QOUT, FMT>(g, s);
-  } else {
-    if (k_groups(g)) return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT, 2>(g, s);
-    if (mid_tiles >= 128) return launch_tiles<PAIR, 128, 128, 32, 64, QOUT, FMT>(g, s);
-    return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT>(g, s);
+  switch (QOUT ? gemm_quantized_route(size_of(g)) : gemm_route(size_of(g))) {
+    case kLargeTiles: return launch_large<PAIR, QOUT, FMT>(g, s);
+    case kMidTiles: return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
+    case kEightWaves: return launch_tiles<PAIR, 128, 128, 32, 64, QOUT, FMT>(g, s);
+    case kThinTiles: return launch_thin<PAIR, QOUT, FMT>(g, s);
+    default: break;
   }
+  if constexpr (QOUT)
+    return hipErrorInvalidValue;
+  else if (gemm_route(size_of(g)) == kTwoKGroups)
+    return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT, 2>(g, s);
+  else
+    return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT>(g, s);
 }
 
 // The kernels address operands with 32-bit offsets: split the problem into
@@ -1729,8 +1625,10 @@ hipError_t launch_grouped_tiles(GemmGroup gs, hipStream_t s) {
 
 template <int PAIR>
 hipError_t launch_grouped_thin(GemmGroup gs, hipStream_t s) {
+  GemmSize sizes[kMaxGroup];
+  for (int i = 0; i < gs.count; ++i) sizes[i] = size_of(gs.prob[i]);
   int64_t rows;
-  return with_thin(thin_config(gs.prob, gs.count, rows), [&](auto ti, auto tj) {
+  return with_thin(thin_config(sizes, gs.count, rows), [&](auto ti, auto tj) {
     constexpr int TI = decltype(ti)::value, TJ = decltype(tj)::value;
     const int64_t total = count_tiles<TI * 16, TJ * 16>(gs);
     if (total <= 0) return hipErrorInvalidValue;
@@ -1762,17 +1660,15 @@ hipError_t launch_grouped_pair(const GemmGroup& gs, hipStream_t s) {
   int64_t big = 0, mid = 0;
   for (int i = 0; i < gs.count; ++i) {
     const GemmArgs& g = gs.prob[i];
-    const int64_t big_i = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-    const int64_t mid_i = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-    const bool skinny = !takes_large(big_i, mid_i) && mid_i <= kCUs;
-    if (skinny && is_thin(g)) {
+    const GemmRoute r = gemm_route(size_of(g));
+    if (r == kThinTiles) {
       thin.prob[thin.count++] = g;
-    } else if (skinny && k_groups(g)) {
+    } else if (r == kTwoKGroups) {
       grouped.prob[grouped.count++] = g;
     } else {
       tiled.prob[tiled.count++] = g;
-      big += big_i;
-      mid += mid_i;
+      big += tile_count(size_of(g), 256, 256);
+      mid += tile_count(size_of(g), 128, 128);
     }
   }
   if (tiled.count) {
@@ -1840,14 +1736,7 @@ hipError_t launch_gemm_quantized(const GemmArgs& g, int pair, hipStream_t s) {
 
 template <int PAIR>
 hipError_t launch_splitk_pair(const GemmArgs& g, unsigned grid, hipStream_t s) {
-  // Thin tiles where they take less time: a split loads 256 K / S bytes per
-  // CU and then pays about 10 us (900 KB of loads) for the partial tiles'
-  // way through memory; the thin tiles' waves meet in LDS.  256 x 12288 x
-  // 4096: split over four 24.9 us, thin 64 x 64 tiles 21.9; 256 x 25600 x
-  // 5120 stays split.
-  int64_t rows;
-  thin_config(&g, 1, rows);
-  if (rows * g.K < 256 * g.K / g.splits + 900000) return launch_thin<PAIR, false, 0>(g, s);
+  if (gemm_splitk_route(size_of(g), g.splits) == kThinTiles) return launch_thin<PAIR, false, 0>(g, s);
   gemm_splitk_kernel<PAIR, 128, 128, 32, 64, 0><<<dim3(grid), 512, 0, s>>>(g);
   return hipGetLastError();
 }
@@ -1868,3 +1757,13 @@ hipError_t launch_gemm_splitk(const GemmArgs& g, int pair, hipStream_t s) {
 }
 
 }  // namespace fp8q
+
+// The GemmRoute of an M x N x K problem, for the tests (no part of the ABI):
+// `form` is a GemmPair of fp8q_gemm and its relatives, 5 fp8q_gemm_quantized,
+// 6 fp8q_gemm_splitk.
+extern "C" int fp8q_gemm_route(int form, int64_t M, int64_t N, int64_t K) {
+  const fp8q::GemmSize s{M, N, K};
+  if (form == 5) return fp8q::gemm_quantized_route(s);
+  if (form == 6) return fp8q::gemm_splitk_route(s, fp8q::gemm_splitk_splits(M, N, K, K, K, N));
+  return fp8q::gemm_route(s);
+}
