@@ -136,13 +136,15 @@ inline GemmRoute gemm_route(const GemmSize& s) {
   return mid >= 128 ? kEightWaves : kSmallTiles;
 }
 
-// Quantized output needs whole 128-column units in a tile: 256 or 128 tiles,
-// or thin tiles of 32 x 128 where the plain call takes thin tiles, whose sums
-// it must repeat (64 x 4096 x 4096, 32 tiles of 128 x 128: 24.8 us, thin
-// 10.9).
+// Quantized output needs whole 128-column units in a tile and must repeat the
+// plain call's sums: 256 or 128 tiles; thin tiles of 32 x 128 where the plain
+// call takes thin tiles (64 x 4096 x 4096, 32 tiles of 128 x 128: 24.8 us,
+// thin 10.9); and where it takes two K groups, eight-wave 128 x 128 tiles that
+// keep both groups' sums (64 x 4096 x 12288 20.4 us, with one sum 20.5; 250 x
+// 512 x 4096 7.2, with one 7.0).
 inline GemmRoute gemm_quantized_route(const GemmSize& s) {
   const GemmRoute r = gemm_route(s);
-  return r == kTwoKGroups || r == kSmallTiles ? kEightWaves : r;
+  return r == kSmallTiles ? kEightWaves : r;
 }
 
 // Split-K over `splits` workgroups per 128 x 128 tile, or thin tiles where

@@ -462,11 +462,14 @@ struct TileLds {
 // their partial tiles are summed in LDS at the end, group 1 into group 0,
 // then group 2, ... (a fixed order).  Each group's step chain (barrier,
 // fragment reads, MFMAs, FMAs) then overlaps the others' on the same SIMDs.
+// SUMS == 2: one group keeps two sums, of every other K block each, and adds
+// them at the end: the sum of two K groups, for a tile shape that cannot take
+// them (quantized output repeats the plain call's sums).
 // SPLITK: the workgroup is split `split` of the g.splits that share tile
 // number `tile`, and sums the K blocks split * KT .. split * KT + KT - 1
 // (KT = K / 128 / g.splits); see splitk_reduce for how the partial tiles
 // meet.
-template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1, bool SPLITK = false>
+template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1, bool SPLITK = false, int SUMS = 1>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, int tm, int tn, int split = 0,
                                           int tile = 0) {
   using Lds = TileLds<PAIR, BM, BN, WM, WN, KS>;  // lds_all: kBytes of it, 1024-byte aligned
@@ -512,11 +515,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, i
   };
   const int mw = (int)m0 + wm, nw = (int)n0 + wn;  // wave's first row / column
 
-  v4f acc[TI][TJ];
+  v4f sums[SUMS][TI][TJ];
 #pragma unroll
-  for (int i = 0; i < TI; ++i)
+  for (int q = 0; q < SUMS; ++q)
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) sums[q][i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  auto& acc = sums[0];
 
   // Scales.  This lane accumulates rows m = mw + 16 i + lane % 16 and
   // columns n = nw + 16 j + 4 (lane / 16) + r.  Per K block kt the row
@@ -634,7 +640,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, i
   // kMore: with two stages, the next stage's A tile and scales go out
   // (kMoreB: and the next-but-one's B tile); with more stages, all loads
   // of stage kt + kStages - 1.
-  auto step = [&](const int kt, auto more_c, auto more_b_c) __attribute__((always_inline)) {
+  auto step = [&](const int kt, v4f (&acc)[TI][TJ], auto more_c, auto more_b_c) __attribute__((always_inline)) {
     constexpr bool kMore = decltype(more_c)::value;
     constexpr bool kMoreB = decltype(more_b_c)::value;
     const int cur_st = kt % kStages, nxt_st = (kt + kStages - 1) % kStages;
@@ -934,15 +940,35 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, i
       // (the B load of step KT-2 re-reads stage KT-1's B tile into a buffer
       // nothing reads again: a third copy of the step body, without it,
       // would push the kernel past its registers)
-      for (; kt + 1 < KT; ++kt) step(kt, std::true_type{}, std::true_type{});
-      step(kt, std::false_type{}, std::false_type{});
+      for (; kt + 1 < KT; ++kt) step(kt, acc, std::true_type{}, std::true_type{});
+      step(kt, acc, std::false_type{}, std::false_type{});
+    } else if constexpr (SUMS == 2) {
+      // KT is even: two K groups have every other K block each
+      for (; kt + kStages < KT; kt += 2) {
+        step(kt, sums[0], std::true_type{}, std::false_type{});
+        step(kt + 1, sums[1], std::true_type{}, std::false_type{});
+      }
+      for (; kt < KT; kt += 2) {
+        if (kt + kStages - 1 < KT)
+          step(kt, sums[0], std::true_type{}, std::false_type{});
+        else
+          step(kt, sums[0], std::false_type{}, std::false_type{});
+        step(kt + 1, sums[1], std::false_type{}, std::false_type{});
+      }
     } else {
-      for (; kt + kStages - 1 < KT; ++kt) step(kt, std::true_type{}, std::false_type{});
-      for (; kt < KT; ++kt) step(kt, std::false_type{}, std::false_type{});
+      for (; kt + kStages - 1 < KT; ++kt) step(kt, acc, std::true_type{}, std::false_type{});
+      for (; kt < KT; ++kt) step(kt, acc, std::false_type{}, std::false_type{});
     }
   };
 
   all_steps();
+
+  if constexpr (SUMS == 2) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) acc[i][j] += sums[SUMS - 1][i][j];
+  }
 
   if constexpr (KS > 1) {
     // the groups' partial tiles: group k > 0 writes its accumulators to LDS
@@ -1257,12 +1283,12 @@ __global__ __launch_bounds__(kThinWaves * 64) void gemm_thin_kernel(GemmArgs g) 
   thin_tile<PAIR, TI, TJ, QOUT, FMT>(g, lds, tm, tn);
 }
 
-template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1>
+template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1, int SUMS = 1>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KS) void gemm_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[TileLds<PAIR, BM, BN, WM, WN, KS>::kBytes];
   int tm, tn;
   tile_coords<BM, BN>(g.M, g.N, g.K, blockIdx.x, tm, tn);
-  gemm_tile<PAIR, BM, BN, WM, WN, QOUT, FMT, KS>(g, lds, tm, tn);
+  gemm_tile<PAIR, BM, BN, WM, WN, QOUT, FMT, KS, false, SUMS>(g, lds, tm, tn);
 }
 
 // Large problems: 256 x 256 tiles, one per CU at a time, so the launch runs
@@ -1372,12 +1398,12 @@ __global__ __launch_bounds__(512) void gemm_grouped_large_kernel(GemmGroup gs, i
   });
 }
 
-template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1>
+template <int PAIR, int BM, int BN, int WM, int WN, bool QOUT, int FMT, int KS = 1, int SUMS = 1>
 hipError_t launch_tiles(const GemmArgs& g, hipStream_t s) {
   const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   if (tiles <= 0 || tiles > 0x7fffffff) return hipErrorInvalidValue;
   constexpr int threads = (BM / WM) * (BN / WN) * 64 * KS;
-  gemm_kernel<PAIR, BM, BN, WM, WN, QOUT, FMT, KS><<<dim3((unsigned)tiles), threads, 0, s>>>(g);
+  gemm_kernel<PAIR, BM, BN, WM, WN, QOUT, FMT, KS, SUMS><<<dim3((unsigned)tiles), threads, 0, s>>>(g);
   return hipGetLastError();
 }
 
@@ -1431,14 +1457,17 @@ hipError_t launch_pair(const GemmArgs& g, hipStream_t s) {
     case kMidTiles: return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
     case kEightWaves: return launch_tiles<PAIR, 128, 128, 32, 64, QOUT, FMT>(g, s);
     case kThinTiles: return launch_thin<PAIR, QOUT, FMT>(g, s);
+    case kTwoKGroups:
+      if constexpr (QOUT)
+        return launch_tiles<PAIR, 128, 128, 32, 64, QOUT, FMT, 1, 2>(g, s);
+      else
+        return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT, 2>(g, s);
+    case kSmallTiles:
+      if constexpr (!QOUT) return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT>(g, s);
+      break;
     default: break;
   }
-  if constexpr (QOUT)
-    return hipErrorInvalidValue;
-  else if (gemm_route(size_of(g)) == kTwoKGroups)
-    return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT, 2>(g, s);
-  else
-    return launch_tiles<PAIR, 64, 64, 32, 32, QOUT, FMT>(g, s);
+  return hipErrorInvalidValue;
 }
 
 // The kernels address operands with 32-bit offsets: split the problem into
@@ -1591,6 +1620,7 @@ FP8Q_GEMM_LARGE(kPairBlockK, false, 3)
 #undef FP8Q_GEMM_LARGE
 template __global__ void gemm_kernel<kPairBlock, 128, 128, 64, 64, true, 0>(GemmArgs);
 template __global__ void gemm_kernel<kPairBlock, 128, 128, 32, 64, true, 0>(GemmArgs);
+template __global__ void gemm_kernel<kPairBlock, 128, 128, 32, 64, true, 0, 1, 2>(GemmArgs);
 #define FP8Q_GEMM_GROUPED(PAIR)                                                     \
   template __global__ void gemm_grouped_large_kernel<PAIR>(GemmGroup, int, int);       \
   template __global__ void gemm_grouped_kernel<PAIR, 128, 128, 64, 64>(GemmGroup);     \
