@@ -1479,7 +1479,9 @@ hipError_t launch_split(const GemmArgs& g, hipStream_t s) {
   const int64_t lim = (int64_t)1 << 31;
   int64_t mstep = g.M, nstep = g.N;
   if (g.M * g.lda >= lim) mstep = ((lim - 1) / g.lda) / 256 * 256;
-  const int64_t c_row_bytes = QOUT ? g.ldq : 2 * g.ldc;
+  // (quantized output is cut where fp8q_gemm with contiguous C, ldc = N, is:
+  // the last cut's kernel, and so its K sums, are then the plain call's)
+  const int64_t c_row_bytes = QOUT && g.ldq > 2 * g.ldc ? g.ldq : 2 * g.ldc;
   if (g.M * c_row_bytes >= lim) {
     const int64_t cstep = ((lim - 1) / c_row_bytes) / 256 * 256;
     if (cstep < mstep) mstep = cstep;

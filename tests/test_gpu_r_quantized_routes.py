@@ -3,7 +3,9 @@ wherever fp8q_gemm sums its K blocks in another order than one after another
 (the thin tiles are held to it beside their other tests).
 
 * Two K groups: ragged rows, an even and an odd 1024-column band (the second
-  walks K backwards), the fewest K blocks and several rounds of the ring."""
+  walks K backwards), the fewest K blocks and several rounds of the ring.
+* A bf16 output of 2 GiB, which fp8q_gemm cuts so that its last 256 rows take
+  another kernel than the rest."""
 import pytest
 import torch
 
@@ -31,3 +33,10 @@ def test_where_gemm_takes_k_groups(shape):
     print("quantized output, K groups", shape, flush=True)
     assert route("block", *shape) == "two K groups"
     check(*shape, seed=1201)
+
+
+def test_where_gemm_cuts_its_output():
+    M, K, N = 1 << 18, 256, 4096
+    print("quantized output, output cut at 2 GiB", flush=True)
+    assert route("block", 256, K, N) == "two K groups" and route("block", M - 256, K, N) == "large"
+    check(M, K, N, seed=1211)
