@@ -35,7 +35,7 @@ inline int64_t tile_count(const GemmSize& s, int bm, int bn) { return ((s.M + bm
 // parts fit in one round of the CUs: up to a quarter of them in four, up to
 // half in two; a fuller last round keeps whole tiles.
 struct LargePlan {
-  int full, parts, grid, cost;
+  int full, parts, grid;
 };
 inline LargePlan large_plan(int64_t total) {
   const int rest = (int)(total % kCUs), rounds = (int)(total / kCUs);
@@ -43,21 +43,53 @@ inline LargePlan large_plan(int64_t total) {
   p.parts = rest == 0 || rest > kCUs / 2 ? 1 : (rest <= kCUs / 4 ? 4 : 2);
   p.full = p.parts == 1 ? (int)total : rounds * kCUs;
   p.grid = p.full + (p.parts == 1 ? 0 : rest * p.parts);
-  p.cost = 100 * rounds + (rest == 0 ? 0 : p.parts == 4 ? 40 : p.parts == 2 ? 62 : 90);
   return p;
 }
 
-// Whether `big` 256 x 256 tiles run before `mid` 128 x 128 tiles (the same
-// outputs) would: both in percent of a whole 256 x 256 tile's time.  512 of
-// the 128 x 128 tiles (four waves, two workgroups per CU) take 59, up to 256
-// (one per CU) 37; a last round of whole 256 x 256 tiles on part of the chip
-// 90 (measured at K = 4096: 192 tiles 47 us, 256 tiles 56 us, 512 of 128 x
-// 128 33 us, 256 of them 20.6 us).
-inline bool takes_large(int64_t big, int64_t mid) {
-  if (big > 0x3fffffff / 100) return true;
-  const int64_t rest = mid % (2 * kCUs);
-  const int64_t cost_mid = 59 * (mid / (2 * kCUs)) + (rest == 0 ? 0 : rest <= kCUs ? 37 : 59);
-  return large_plan(big).cost < cost_mid;
+// Whether a launch of `outputs` outputs takes less time in `big` tiles of 256
+// x 256 than in `mid` tiles of 128 x 128 (four waves).  Estimates in ns, fitted
+// to both kernels' times at 4600 random sizes with more than 256 of the latter
+// (K 128 to 25600, every pair; 7% from them, their ratio 5%): a round of kCUs
+// large tiles, or of two 128 x 128 tiles per CU, takes a constant and a time
+// per K block (kBlockNs); a last round a share of that which grows with how
+// full it is.  Short K is the 128 x 128 tiles': a large tile's first loads and
+// its epilogue overlap nothing (16384 x 128 x 6144, 1x128 x 1x128: 64.1 us on
+// large tiles, 49.7 on the others; 3000 x 128 x 8192, 1x128 x 128x128: 15.5 and
+// 12.4; at K = 4096 1x128 x 1x128 455 and 400 the other way).  Within 2% the
+// side that holds on more of the sizes: large from 512 tiles on and where they
+// fill whole rounds.  1% of those sizes are more than 2.5% slower than with the
+// rule "large from 512 tiles on, 1x128 x 1x128 never"; 15% were with estimates
+// of K = 4096 for every K.
+struct BlockNs {
+  int large, mid;
+};
+constexpr BlockNs kBlockNs[6] = {{1614, 892},   // tensor
+                                 {1614, 892},   // row
+                                 {1814, 1031},  // 1x128 x 128x128
+                                 {2204, 1152},  // 1x128 x 1x128
+                                 {1708, 983},   // power-of-two scales
+                                 {1944, 1072}}; // quantized output
+constexpr int kFormQuantized = 5;  // after the GemmPair values
+
+inline bool takes_large(int form, int64_t big, int64_t mid, int64_t outputs, int64_t K) {
+  if (mid <= kCUs) return false;
+  const double kb = (double)(K / kBlockK), common = form == kFormQuantized ? 2890 + outputs * (8240 / 16777216.0)
+                                                                           : 2161 + outputs * (4506 / 16777216.0);
+  const double l = kBlockNs[form].large * kb, m = kBlockNs[form].mid * kb;
+  const int64_t rest = big % kCUs, rest_mid = mid % (2 * kCUs);
+  const double fill = rest / (double)kCUs, fill_mid = rest_mid / (2.0 * kCUs);
+  double large = common + (big / kCUs) * (2757 + l), tiled = common + (mid / (2 * kCUs)) * (641 + m);
+  if (rest > kCUs / 2)
+    large += 2452 + l * (0.566 + 0.357 * fill);
+  else if (rest > kCUs / 4)
+    large += 1561 + l * (0.486 + 0.159 * fill);
+  else if (rest > 0)
+    large += 1884 + l * (0.201 + 0.416 * fill);
+  if (rest_mid > kCUs)
+    tiled += 1043 + m * (0.897 + 0.109 * fill_mid);
+  else if (rest_mid > 0)
+    tiled += 1404 + m * (0.472 + 0.099 * fill_mid);
+  return large < tiled * (big >= 2 * kCUs || rest == 0 ? 1.02 : 0.98);
 }
 
 // Two K groups per 64 x 64 tile (one workgroup of 8 waves per CU) when there
@@ -127,9 +159,9 @@ inline bool is_thin(const GemmSize& s) {
 // four-stage ring (one workgroup per CU) when there are 128 to 256 of them
 // (1024 x 4096 x 4096, 256 tiles: 22.2 us, with 4 waves 24.6), and 64 x 64
 // tiles (4 waves of 32 x 32) below that.
-inline GemmRoute gemm_route(const GemmSize& s) {
+inline GemmRoute gemm_route(int form, const GemmSize& s) {
   const int64_t mid = tile_count(s, 128, 128);
-  if (takes_large(tile_count(s, 256, 256), mid)) return kLargeTiles;
+  if (takes_large(form, tile_count(s, 256, 256), mid, s.M * s.N, s.K)) return kLargeTiles;
   if (mid > kCUs) return kMidTiles;
   if (is_thin(s)) return kThinTiles;
   if (k_groups(s)) return kTwoKGroups;
@@ -143,7 +175,7 @@ inline GemmRoute gemm_route(const GemmSize& s) {
 // keep both groups' sums (64 x 4096 x 12288 20.4 us, with one sum 20.5; 250 x
 // 512 x 4096 7.2, with one 7.0).
 inline GemmRoute gemm_quantized_route(const GemmSize& s) {
-  const GemmRoute r = gemm_route(s);
+  const GemmRoute r = gemm_route(kFormQuantized, s);
   return r == kSmallTiles ? kEightWaves : r;
 }
 
@@ -152,8 +184,8 @@ inline GemmRoute gemm_quantized_route(const GemmSize& s) {
 // about 10 us (900 KB of loads) for the partial tiles' way through memory; the
 // thin tiles' waves meet in LDS.  256 x 12288 x 4096: split over four 24.9 us,
 // thin 64 x 64 tiles 21.9; 256 x 25600 x 5120 stays split.
-inline GemmRoute gemm_splitk_route(const GemmSize& s, int splits) {
-  if (splits <= 1) return gemm_route(s);
+inline GemmRoute gemm_splitk_route(int form, const GemmSize& s, int splits) {
+  if (splits <= 1) return gemm_route(form, s);
   int64_t rows;
   thin_config(&s, 1, rows);
   return rows * s.K < 256 * s.K / splits + 900000 ? kThinTiles : kSplitK;

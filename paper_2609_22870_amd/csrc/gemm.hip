@@ -1452,7 +1452,7 @@ hipError_t launch_thin(const GemmArgs& g, hipStream_t s) {
 
 template <int PAIR, bool QOUT, int FMT>
 hipError_t launch_pair(const GemmArgs& g, hipStream_t s) {
-  switch (QOUT ? gemm_quantized_route(size_of(g)) : gemm_route(size_of(g))) {
+  switch (QOUT ? gemm_quantized_route(size_of(g)) : gemm_route(PAIR, size_of(g))) {
     case kLargeTiles: return launch_large<PAIR, QOUT, FMT>(g, s);
     case kMidTiles: return launch_tiles<PAIR, 128, 128, 64, 64, QOUT, FMT>(g, s);
     case kEightWaves: return launch_tiles<PAIR, 128, 128, 32, 64, QOUT, FMT>(g, s);
@@ -1689,10 +1689,10 @@ hipError_t launch_grouped_large(GemmGroup gs, hipStream_t s) {
 template <int PAIR>
 hipError_t launch_grouped_pair(const GemmGroup& gs, hipStream_t s) {
   GemmGroup tiled{}, thin{}, grouped{};
-  int64_t big = 0, mid = 0;
+  int64_t big = 0, mid = 0, outputs = 0;
   for (int i = 0; i < gs.count; ++i) {
     const GemmArgs& g = gs.prob[i];
-    const GemmRoute r = gemm_route(size_of(g));
+    const GemmRoute r = gemm_route(PAIR, size_of(g));
     if (r == kThinTiles) {
       thin.prob[thin.count++] = g;
     } else if (r == kTwoKGroups) {
@@ -1701,12 +1701,13 @@ hipError_t launch_grouped_pair(const GemmGroup& gs, hipStream_t s) {
       tiled.prob[tiled.count++] = g;
       big += tile_count(size_of(g), 256, 256);
       mid += tile_count(size_of(g), 128, 128);
+      outputs += g.M * g.N;
     }
   }
   if (tiled.count) {
-    const hipError_t e = takes_large(big, mid) ? launch_grouped_large<PAIR>(tiled, s)
-                         : mid >= 256          ? launch_grouped_tiles<PAIR, 128, 128, 64, 64>(tiled, s)
-                                               : launch_grouped_tiles<PAIR, 64, 64, 32, 32>(tiled, s);
+    const hipError_t e = takes_large(PAIR, big, mid, outputs, gs.prob[0].K) ? launch_grouped_large<PAIR>(tiled, s)
+                         : mid >= 256 ? launch_grouped_tiles<PAIR, 128, 128, 64, 64>(tiled, s)
+                                      : launch_grouped_tiles<PAIR, 64, 64, 32, 32>(tiled, s);
     if (e != hipSuccess) return e;
   }
   if (thin.count) {
@@ -1768,7 +1769,7 @@ hipError_t launch_gemm_quantized(const GemmArgs& g, int pair, hipStream_t s) {
 
 template <int PAIR>
 hipError_t launch_splitk_pair(const GemmArgs& g, unsigned grid, hipStream_t s) {
-  if (gemm_splitk_route(size_of(g), g.splits) == kThinTiles) return launch_thin<PAIR, false, 0>(g, s);
+  if (gemm_splitk_route(PAIR, size_of(g), g.splits) == kThinTiles) return launch_thin<PAIR, false, 0>(g, s);
   gemm_splitk_kernel<PAIR, 128, 128, 32, 64, 0><<<dim3(grid), 512, 0, s>>>(g);
   return hipGetLastError();
 }
@@ -1791,11 +1792,11 @@ hipError_t launch_gemm_splitk(const GemmArgs& g, int pair, hipStream_t s) {
 }  // namespace fp8q
 
 // The GemmRoute of an M x N x K problem, for the tests (no part of the ABI):
-// `form` is a GemmPair of fp8q_gemm and its relatives, 5 fp8q_gemm_quantized,
-// 6 fp8q_gemm_splitk.
+// `form` is a GemmPair of fp8q_gemm and its relatives, kFormQuantized, or that
+// plus one and a GemmPair for fp8q_gemm_splitk.
 extern "C" int fp8q_gemm_route(int form, int64_t M, int64_t N, int64_t K) {
   const fp8q::GemmSize s{M, N, K};
-  if (form == 5) return fp8q::gemm_quantized_route(s);
-  if (form == 6) return fp8q::gemm_splitk_route(s, fp8q::gemm_splitk_splits(M, N, K, K, K, N));
-  return fp8q::gemm_route(s);
+  if (form == fp8q::kFormQuantized) return fp8q::gemm_quantized_route(s);
+  if (form < fp8q::kFormQuantized) return fp8q::gemm_route(form, s);
+  return fp8q::gemm_splitk_route(form - fp8q::kFormQuantized - 1, s, fp8q::gemm_splitk_splits(M, N, K, K, K, N));
 }

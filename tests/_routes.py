@@ -6,7 +6,8 @@ import ctypes
 import paper_2609_22870_amd as fp8q
 
 NAMES = ("large", "mid", "eight waves", "small", "two K groups", "thin", "split-K")
-FORMS = {"tensor": 0, "row": 1, "block": 2, "blockk": 3, "pow2": 4, "quantized": 5, "splitk": 6}
+FORMS = {"tensor": 0, "row": 1, "block": 2, "blockk": 3, "pow2": 4, "quantized": 5, "splitk tensor": 6,
+         "splitk row": 7, "splitk block": 8, "splitk blockk": 9}
 
 
 def route(form, M, K, N):

