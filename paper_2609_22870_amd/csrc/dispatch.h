@@ -72,7 +72,8 @@ constexpr BlockNs kBlockNs[6] = {{1614, 892},   // tensor
 constexpr int kFormQuantized = 5;  // after the GemmPair values
 
 inline bool takes_large(int form, int64_t big, int64_t mid, int64_t outputs, int64_t K) {
-  if (mid <= kCUs) return false;
+  // (one round of halves alone: 2 to 11% slower at every K)
+  if (mid <= kCUs || big <= kCUs / 2) return false;
   const double kb = (double)(K / kBlockK), common = form == kFormQuantized ? 2890 + outputs * (8240 / 16777216.0)
                                                                            : 2161 + outputs * (4506 / 16777216.0);
   const double l = kBlockNs[form].large * kb, m = kBlockNs[form].mid * kb;
@@ -99,55 +100,75 @@ inline bool takes_large(int form, int64_t big, int64_t mid, int64_t outputs, int
 // measured faster there).
 inline bool k_groups(const GemmSize& s) { return tile_count(s, 64, 64) <= kCUs && (s.K / kBlockK) % 2 == 0; }
 
-// Operand rows (of K bytes) that the busiest CU loads: its tiles times a
-// tile's rows of A (none past M) and of B.
-inline int64_t cu_rows(int64_t tiles, int64_t rows) { return (tiles + kCUs - 1) / kCUs * rows; }
+// Time of the kernels for problems of at most kCUs 128 x 128 tiles, in ns: a
+// constant, and for each round of one tile per CU a constant (first loads,
+// epilogue, the meeting of partial tiles), a step per K block of a wave's
+// chain, and the bytes that the CU loads, (bm + bn) K.  Fitted to all of these
+// kernels' times at 8700 random sizes (K 128 to 25600, every pair, weights
+// rotated through 3 x up to 160 MB), to choose well among them: the choice is
+// 1.2% above the best of them on average (1.8% with the operand rows per CU
+// alone, which sent short K to thin tiles: 192 x 128 x 8192 7.7 us, here 4.2;
+// 27% with no thin tiles).
+struct TileCost {
+  int bm, bn, chain;  // chain: K blocks of one step of every wave
+  int base, round, step, load;  // load: per 100 KB
+};
+constexpr TileCost kEightWavesCost = {128, 128, 1, 1468, 1889, 350, 337};
+constexpr TileCost kTwoKGroupsCost = {64, 64, 2, 826, 2050, 0, 36};  // (step: kTwoKGroupsStep)
+constexpr TileCost kSmallTilesCost = {64, 64, 1, 2185, 489, 220, 62};
+constexpr TileCost kThinCost[kThinConfigs] = {{16, 16, 8, 2342, 156, 195, 233},
+                                              {16, 32, 8, 2336, 94, 245, 597},
+                                              {32, 32, 8, 2160, 554, 325, 717},
+                                              {32, 64, 8, 1056, 1577, 488, 705},
+                                              {64, 64, 8, 820, 2569, 685, 727}};
 
-// The thin tile whose busiest CU loads the fewest rows, for the problems of
-// one launch (one K).  64 x 64, whose partial tiles take longest to meet,
-// from eight K blocks a wave on (256 x 12288 x 4096: 21.8 us against 23.5
-// with two K groups; 64 x 4096 x 12288: 12.6 against 10.9).
-inline int thin_config(const GemmSize* probs, int count, int64_t& rows) {
+// Two K groups' step by form (the pairs' vector operations show there): thin
+// 64 x 64 tiles, which take as long at K = 8192 with block scales, do so from
+// 17408 with tensor and row scales.
+constexpr int kTwoKGroupsStep[6] = {385, 385, 416, 400, 416, 416};
+
+// `rounds`: of one tile per CU
+inline double tile_ns(const TileCost& c, double rounds, int64_t K) {
+  const int64_t steps = (K / kBlockK + c.chain - 1) / c.chain;
+  return c.base + rounds * (c.round + c.step * (double)steps + c.load * (c.bm + c.bn) * (K / 1e5));
+}
+
+// The thin tile that takes the least time for the problems of one launch (of
+// one K), and that time.
+inline int thin_config(const GemmSize* probs, int count, double& ns) {
   int best = 0;
   for (int c = 0; c < kThinConfigs; ++c) {
-    if (c == kThin64x64 && probs[0].K < 8 * 8 * kBlockK) continue;
-    int64_t tiles = 0, most = 0;
-    for (int i = 0; i < count; ++i) {
-      tiles += tile_count(probs[i], kThinM[c], kThinN[c]);
-      const int64_t per = (probs[i].M < kThinM[c] ? probs[i].M : kThinM[c]) + kThinN[c];
-      most = per > most ? per : most;
-    }
-    const int64_t r = cu_rows(tiles, most);
-    if (c == 0 || r < rows) {
+    int64_t tiles = 0;
+    for (int i = 0; i < count; ++i) tiles += tile_count(probs[i], kThinM[c], kThinN[c]);
+    const double t = tile_ns(kThinCost[c], (double)((tiles + kCUs - 1) / kCUs), probs[0].K);
+    if (c == 0 || t < ns) {
       best = c;
-      rows = r;
+      ns = t;
     }
   }
   return best;
 }
 
+// Few rows against weights too large to stay in the last-level cache between
+// calls: thin tiles, which read each weight row in pieces of 1 KB or less,
+// take this much longer (33 to 80 x 25600 x 5120: 40-48 us, split 37-44; 24 x
+// 12288 x 12288: 35, with two K groups 32).
+inline double thin_from_memory(const GemmSize& s) { return s.M <= 128 && (s.M + s.N) * s.K > 100000000 ? 1.2 : 1.0; }
+
 // Whether a problem too small for the 128 x 128 tiles of four waves is thin:
-// the tile kernels load fewer rows per CU only where they have tiles for most
-// of the CUs, and take longer per row: 1.13 times for 64 x 64 with two K
-// groups, 1.2 for 64 x 64 without (two workgroups per CU, which even out),
-// 1.33 for 128 x 128 with eight waves (measured: 75, 70 and 64 KB a
-// microsecond and CU against 85).  64 x 4096 x 12288 (192 tiles of 64 x 64)
-// stays: 10.9 us, thin 32 x 32 13.2; 128 x 4096 x 12288 (384 of 64 x 64):
-// 15.1, thin 19.2; 256 x 4096 x 12288 (192 of 128 x 128): 19.4, thin 26.9; 64
-// x 12288 x 4096 (64 tiles) 22.2 and 11.9.
-inline bool is_thin(const GemmSize& s) {
+// against the kernel it takes else (see gemm_route).  Of 64 x 64 tiles without
+// K groups two workgroups share a CU and even out.
+inline bool is_thin(int form, const GemmSize& s) {
   const int64_t t64 = tile_count(s, 64, 64), mid = tile_count(s, 128, 128);
-  const int64_t rows64 = (s.M < 64 ? s.M : 64) + 64;
-  int64_t tiled;  // in percent
+  double tiled, thin;
   if (k_groups(s))
-    tiled = cu_rows(t64, rows64) * 113;
+    tiled = tile_ns(kTwoKGroupsCost, 1.0, s.K) + kTwoKGroupsStep[form] * (double)(s.K / (2 * kBlockK));
   else if (mid >= 128)
-    tiled = cu_rows(mid, (s.M < 128 ? s.M : 128) + 128) * 133;
+    tiled = tile_ns(kEightWavesCost, 1.0, s.K);
   else
-    tiled = t64 > kCUs ? t64 * rows64 * 120 / kCUs : rows64 * 120;
-  int64_t rows;
-  thin_config(&s, 1, rows);
-  return rows * 100 < tiled;
+    tiled = tile_ns(kSmallTilesCost, t64 > kCUs ? t64 / (double)kCUs : 1.0, s.K);
+  thin_config(&s, 1, thin);
+  return thin * thin_from_memory(s) < tiled;
 }
 
 // 256 x 256 tiles (8 waves of 128 x 64, see large_tiles) where they take less
@@ -163,7 +184,7 @@ inline GemmRoute gemm_route(int form, const GemmSize& s) {
   const int64_t mid = tile_count(s, 128, 128);
   if (takes_large(form, tile_count(s, 256, 256), mid, s.M * s.N, s.K)) return kLargeTiles;
   if (mid > kCUs) return kMidTiles;
-  if (is_thin(s)) return kThinTiles;
+  if (is_thin(form, s)) return kThinTiles;
   if (k_groups(s)) return kTwoKGroups;
   return mid >= 128 ? kEightWaves : kSmallTiles;
 }
@@ -186,8 +207,10 @@ inline GemmRoute gemm_quantized_route(const GemmSize& s) {
 // thin 64 x 64 tiles 21.9; 256 x 25600 x 5120 stays split.
 inline GemmRoute gemm_splitk_route(int form, const GemmSize& s, int splits) {
   if (splits <= 1) return gemm_route(form, s);
-  int64_t rows;
-  thin_config(&s, 1, rows);
+  double ns;
+  const int c = thin_config(&s, 1, ns);
+  const int64_t tiles = tile_count(s, kThinM[c], kThinN[c]);
+  const int64_t rows = (tiles + kCUs - 1) / kCUs * ((s.M < kThinM[c] ? s.M : kThinM[c]) + kThinN[c]);
   return rows * s.K < 256 * s.K / splits + 900000 ? kThinTiles : kSplitK;
 }
 

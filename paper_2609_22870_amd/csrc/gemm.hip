@@ -1445,8 +1445,8 @@ hipError_t launch_thin(const GemmArgs& g, hipStream_t s) {
     return launch(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
   } else {
     const GemmSize size = size_of(g);
-    int64_t rows;
-    return with_thin(thin_config(&size, 1, rows), launch);
+    double ns;
+    return with_thin(thin_config(&size, 1, ns), launch);
   }
 }
 
@@ -1659,8 +1659,8 @@ template <int PAIR>
 hipError_t launch_grouped_thin(GemmGroup gs, hipStream_t s) {
   GemmSize sizes[kMaxGroup];
   for (int i = 0; i < gs.count; ++i) sizes[i] = size_of(gs.prob[i]);
-  int64_t rows;
-  return with_thin(thin_config(sizes, gs.count, rows), [&](auto ti, auto tj) {
+  double ns;
+  return with_thin(thin_config(sizes, gs.count, ns), [&](auto ti, auto tj) {
     constexpr int TI = decltype(ti)::value, TJ = decltype(tj)::value;
     const int64_t total = count_tiles<TI * 16, TJ * 16>(gs);
     if (total <= 0) return hipErrorInvalidValue;

@@ -36,3 +36,25 @@ def test_short_k_stays_off_large_tiles(form):
     if form == "blockk":
         for M, N in ((8192, 4096), (16384, 6144), (16384, 12288), (4096, 17408)):
             assert [route(form, M, K, N) for K in (128, 512, 16384)] == ["mid", "mid", "large"], (M, N)
+
+
+def test_quantized_output_sums_as_the_plain_call():
+    """The thin tiles and the two K groups have sum orders of their own: both
+    calls take them at the same sizes, everywhere."""
+    rng = random.Random(6)
+    for _ in range(20000):
+        M, K, N = int(2 ** rng.uniform(0, 11)), 128 * int(2 ** rng.uniform(0, 8)), 128 * int(2 ** rng.uniform(0, 8))
+        plain, quantized = route("block", M, K, N), route("quantized", M, K, N)
+        own = ("thin", "two K groups")
+        assert (plain if plain in own else None) == (quantized if quantized in own else None), (M, K, N)
+
+
+@pytest.mark.parametrize("form", ["tensor", "row", "block", "blockk", "pow2"])
+def test_short_k_stays_off_thin_tiles(form):
+    """A hundred or two rows, a wide output and a few K blocks: 40 to 85%
+    longer on thin tiles than on 64 x 64 or eight-wave 128 x 128 ones; and
+    the problems that thin tiles are for."""
+    for M, K, N in ((192, 128, 8192), (160, 256, 8192), (192, 512, 8192), (8, 128, 25600)):
+        assert route(form, M, K, N) != "thin", (M, K, N)
+    for M, K, N in ((8, 4096, 6144), (16, 12288, 4096), (64, 12288, 4096), (256, 1024, 1024), (256, 12288, 2048)):
+        assert route(form, M, K, N) == "thin", (M, K, N)
