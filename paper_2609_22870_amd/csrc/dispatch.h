@@ -153,7 +153,7 @@ inline int thin_config(const GemmSize* probs, int count, double& ns) {
 // calls: thin tiles, which read each weight row in pieces of 1 KB or less,
 // take this much longer (33 to 80 x 25600 x 5120: 40-48 us, split 37-44; 24 x
 // 12288 x 12288: 35, with two K groups 32).
-inline double thin_from_memory(const GemmSize& s) { return s.M <= 128 && (s.M + s.N) * s.K > 100000000 ? 1.2 : 1.0; }
+inline double thin_from_memory(const GemmSize& s) { return s.M <= 128 && (s.M + s.N) * s.K > 80000000 ? 1.2 : 1.0; }
 
 // Whether a problem too small for the 128 x 128 tiles of four waves is thin:
 // against the kernel it takes else (see gemm_route).  Of 64 x 64 tiles without
@@ -201,17 +201,17 @@ inline GemmRoute gemm_quantized_route(const GemmSize& s) {
 }
 
 // Split-K over `splits` workgroups per 128 x 128 tile, or thin tiles where
-// they take less time: a split loads 256 K / S bytes per CU and then pays
-// about 10 us (900 KB of loads) for the partial tiles' way through memory; the
-// thin tiles' waves meet in LDS.  256 x 12288 x 4096: split over four 24.9 us,
-// thin 64 x 64 tiles 21.9; 256 x 25600 x 5120 stays split.
+// they take less time.  A split's time in ns, fitted to 3000 random sizes (11%
+// from them): its share of the K steps, and about 8 us and 0.8 per part for
+// the partial tiles' way through memory; the thin tiles' waves meet in LDS.
+// 256 x 12288 x 4096: split over four 24.9 us, thin 64 x 64 tiles 21.9; 64 x
+// 25600 x 5120: split over four 42.0, thin 49.6.  The choice is 0.4% above the
+// better on average (2.8% with a rule on bytes per CU alone).
 inline GemmRoute gemm_splitk_route(int form, const GemmSize& s, int splits) {
   if (splits <= 1) return gemm_route(form, s);
-  double ns;
-  const int c = thin_config(&s, 1, ns);
-  const int64_t tiles = tile_count(s, kThinM[c], kThinN[c]);
-  const int64_t rows = (tiles + kCUs - 1) / kCUs * ((s.M < kThinM[c] ? s.M : kThinM[c]) + kThinN[c]);
-  return rows * s.K < 256 * s.K / splits + 900000 ? kThinTiles : kSplitK;
+  double thin;
+  thin_config(&s, 1, thin);
+  return thin * thin_from_memory(s) < 7850 + 530.0 * (s.K / kBlockK) / splits + 811.0 * splits ? kThinTiles : kSplitK;
 }
 
 }  // namespace fp8q

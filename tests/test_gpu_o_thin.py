@@ -92,7 +92,7 @@ def test_thin_grouped(M, K):
     check_group([x] * 4, ws, B1, B128, label="thin grouped")
 
 
-@pytest.mark.parametrize("shape", [(2, 250, 7168, 5120), (4, 200, 16384, 4096), (8, 250, 16384, 2048)])
+@pytest.mark.parametrize("shape", [(2, 250, 7168, 5120), (4, 200, 16384, 4096), (8, 43, 32768, 3072)])
 @pytest.mark.parametrize("pair", ["block", "row"])
 def test_split_still_chosen(pair, shape):
     splits, M, K, N = shape
