@@ -11,6 +11,7 @@ import paper_2609_22870_amd as fp8q
 from paper_2609_22870_amd import synth
 
 import _par
+from _routes import route
 
 pytestmark = pytest.mark.gpu
 
@@ -67,6 +68,23 @@ def test_mixed_tiled_and_k_group_problems():
     w2 = synth.weights(384, 512, seed=216, device=DEV)
     check_group([x1, x2], [w1, w2], fp8q.BLOCK_1x128, fp8q.BLOCK_128x128, rows=_par.sample_rows(192),
                 label="mixed tiled and K groups")
+
+
+@pytest.mark.parametrize("ga,gb", [(fp8q.BLOCK_1x128, fp8q.BLOCK_128x128), (fp8q.ROW, fp8q.ROW),
+                                   (fp8q.TENSOR, fp8q.TENSOR)])
+@pytest.mark.parametrize("M,K,ns", [(190, 4096, (4096, 256, 256)), (99, 5120, (1024, 5120, 1024)),
+                                    (129, 256, (128, 4096, 384)), (250, 4096, (4096, 1024, 256))])
+def test_k_group_and_thin_problems(ga, gb, M, K, ns):
+    """Fused projections of which a single call splits the wide one into two K
+    groups and gives the narrow ones thin tiles: one launch where their 64 x
+    64 tiles fit one round of the chip, two where they do not (the last), each
+    output still fp8q_gemm's bit for bit."""
+    form = {fp8q.TENSOR: "tensor", fp8q.ROW: "row"}.get(ga, "block")
+    tiles = -(-M // 64) * sum(n // 64 for n in ns)
+    assert {route(form, M, K, n) for n in ns} == {"two K groups", "thin"} and (tiles <= 256) == (M != 250)
+    x = synth.activations(M, K, seed=251, outlier_seed=252, device=DEV)
+    ws = [synth.weights(n, K, seed=253 + i, device=DEV) for i, n in enumerate(ns)]
+    check_group([x] * 3, ws, ga, gb, rows=np.append(np.arange(0, M, 17), M - 1), label="K groups and thin")
 
 
 def test_distinct_inputs_and_sizes():
