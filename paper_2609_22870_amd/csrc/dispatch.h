@@ -55,9 +55,11 @@ inline LargePlan large_plan(int64_t total) {
 // full it is.  Short K is the 128 x 128 tiles': a large tile's first loads and
 // its epilogue overlap nothing (16384 x 128 x 6144, 1x128 x 1x128: 64.1 us on
 // large tiles, 49.7 on the others; 3000 x 128 x 8192, 1x128 x 128x128: 15.5 and
-// 12.4; at K = 4096 1x128 x 1x128 455 and 400 the other way).  Within 2% the
-// side that holds on more of the sizes: large from 512 tiles on and where they
-// fill whole rounds.  1% of those sizes are more than 2.5% slower than with the
+// 12.4; at K = 4096 1x128 x 1x128 455 and 400 the other way).  Within a few
+// percent the side that holds on more of the sizes: large from 512 tiles on,
+// where they fill whole rounds or a last one in halves, and for one long round
+// that more than 512 of the others would need two for (K >= 3072; measured 0.85 to 0.98 of them, not
+// with 1x128 x 1x128 scales: 0.92 to 1.04).  1% of those sizes are more than 2.5% slower than with the
 // rule "large from 512 tiles on, 1x128 x 1x128 never"; 15% were with estimates
 // of K = 4096 for every K.
 struct BlockNs {
@@ -69,7 +71,8 @@ constexpr BlockNs kBlockNs[6] = {{1614, 892},   // tensor
                                  {2204, 1152},  // 1x128 x 1x128
                                  {1708, 983},   // power-of-two scales
                                  {1944, 1072}}; // quantized output
-constexpr int kFormQuantized = 5;  // after the GemmPair values
+// forms: the GemmPair values, then
+constexpr int kFormQuantized = 5;
 
 inline bool takes_large(int form, int64_t big, int64_t mid, int64_t outputs, int64_t K) {
   // (one round of halves alone: 2 to 11% slower at every K)
@@ -90,7 +93,9 @@ inline bool takes_large(int form, int64_t big, int64_t mid, int64_t outputs, int
     tiled += 1043 + m * (0.897 + 0.109 * fill_mid);
   else if (rest_mid > 0)
     tiled += 1404 + m * (0.472 + 0.099 * fill_mid);
-  return large < tiled * (big >= 2 * kCUs || rest == 0 ? 1.02 : 0.98);
+  const bool one_long = big < kCUs && mid > 2 * kCUs && K >= 24 * kBlockK && form != 3;
+  const bool even = rest == 0 || (rest > kCUs / 4 && rest <= kCUs / 2 && K >= 8 * kBlockK);
+  return large < tiled * (one_long ? 1.05 : big >= 2 * kCUs || even ? 1.02 : 0.98);
 }
 
 // Two K groups per 64 x 64 tile (one workgroup of 8 waves per CU) when there
@@ -152,8 +157,9 @@ inline int thin_config(const GemmSize* probs, int count, double& ns) {
 // Few rows against weights too large to stay in the last-level cache between
 // calls: thin tiles, which read each weight row in pieces of 1 KB or less,
 // take this much longer (33 to 80 x 25600 x 5120: 40-48 us, split 37-44; 24 x
-// 12288 x 12288: 35, with two K groups 32).
-inline double thin_from_memory(const GemmSize& s) { return s.M <= 128 && (s.M + s.N) * s.K > 80000000 ? 1.2 : 1.0; }
+// 12288 x 12288: 35, with two K groups 32; 128 x 25600 x 5120: 62, with two K
+// groups 65).
+inline double thin_from_memory(const GemmSize& s) { return s.M <= 96 && (s.M + s.N) * s.K > 80000000 ? 1.2 : 1.0; }
 
 // Whether a problem too small for the 128 x 128 tiles of four waves is thin:
 // against the kernel it takes else (see gemm_route).  Of 64 x 64 tiles without
