@@ -1,4 +1,4 @@
-// Which kernel a GEMM takes: rules on sizes alone, on the host.
+// Which kernel a call takes: rules on sizes alone, on the host.
 #pragma once
 
 #include <stdint.h>
@@ -218,6 +218,20 @@ inline GemmRoute gemm_splitk_route(int form, const GemmSize& s, int splits) {
   double thin;
   thin_config(&s, 1, thin);
   return thin * thin_from_memory(s) < 7850 + 530.0 * (s.K / kBlockK) / splits + 811.0 * splits ? kThinTiles : kSplitK;
+}
+
+// 1x128 quantization, plain layout: two rows a thread instead of eight.  Up
+// to kFewTiles tiles of 32 x 512, where the few waves of the other kernel and
+// its long encode between loads and stores show (16384 x 4096, the largest
+// measured, 37.4 -> 35.7 us); of many short rows a wave covers two instead of
+// eight, and past these lines that is slower (131072 x 128 20.8 us with eight
+// rows, 23.7 with two; 40000 x 128 8.65 and 9.26; 8192 x 128 3.80 and 3.51;
+// 131072 x 512 33.4 and 34.3; 40000 x 512 12.1 and 11.8).
+constexpr int kQuantRows = 32, kQuantCols = 512;  // a tile of the eight-row kernel
+constexpr int64_t kFewTiles = 4096;
+inline bool takes_few_rows(int64_t rows, int64_t cols) {
+  const int64_t tiles = ((cols + kQuantCols - 1) / kQuantCols) * ((rows + kQuantRows - 1) / kQuantRows);
+  return tiles <= kFewTiles && rows <= (cols < kQuantCols ? 8192 : 65536);
 }
 
 }  // namespace fp8q

@@ -16,6 +16,7 @@
 // array, which the cast overwrites afterwards (in `scales` when each unit
 // has a single partial).
 #include "device_common.h"
+#include "dispatch.h"
 #include "internal.h"
 
 namespace fp8q {
@@ -23,7 +24,7 @@ namespace fp8q {
 namespace quant_detail {
 
 constexpr int kTile = 128;
-constexpr int kWideRows = 32, kWideCols = 512;
+constexpr int kWideRows = kQuantRows, kWideCols = kQuantCols;
 constexpr int kThreads = 256;
 
 enum Kind { kBlock1x128, kBlock128x1, kBlock128x128, kPreTensor, kPreRow, kPreCol };
@@ -338,18 +339,15 @@ __global__ __launch_bounds__(kThreads) void quant_tile_kernel(QuantArgs a) {
   }
 }
 
-// 1x128 units, plain layout, up to kFewTiles tiles of 32 x 512: a thread
+// 1x128 units, plain layout, where takes_few_rows says so: a thread
 // takes two rows instead of eight, so that there are four times the waves and
 // each encodes 16 elements, not 64, between its loads and its stores.  A
 // workgroup covers 8 rows x 512 columns, wave w rows 2w and 2w + 1.  Every
 // lane forms its unit's S and 1/S itself (eight rows shared them by shuffles).
 // Back to back, eight rows and two: 256 x 12288 3.98 -> 3.58 us, 2048 x 4096
 // 7.37 -> 6.44, 3001 x 5120 10.98 -> 9.55, 8192 x 4096 19.98 -> 18.64, 16384 x
-// 4096 37.4 -> 35.7 (5.6 TB/s; a copy reaches 5.2).  The line is the largest
-// size measured; past it, where the kernel is one long stream either way, and
-// where rows / 8 could pass the grid's limit, the eight-row kernel stays.
+// 4096 37.4 -> 35.7 (5.6 TB/s; a copy reaches 5.2).
 constexpr int kFewRows = 2;
-constexpr int64_t kFewTiles = 4096;
 
 template <bool E5>
 __global__ __launch_bounds__(kThreads) void quant_few_kernel(QuantArgs a) {
@@ -722,7 +720,7 @@ hipError_t launch_quantize_fmt(const QuantArgs& a, int granularity, bool trans, 
   (void)nscales;
   switch (granularity) {
     case 3:
-      if (!trans && ((a.cols + kWideCols - 1) / kWideCols) * ((a.rows + kWideRows - 1) / kWideRows) <= kFewTiles) {
+      if (!trans && takes_few_rows(a.rows, a.cols)) {
         constexpr int64_t rows = kThreads / 64 * kFewRows;
         const dim3 grid((unsigned)((a.cols + kWideCols - 1) / kWideCols), (unsigned)((a.rows + rows - 1) / rows));
         quant_few_kernel<E5><<<grid, kThreads, 0, s>>>(a);
@@ -778,3 +776,7 @@ hipError_t launch_cast_f32(const float* x, int64_t n, float scale, bool e5m2, ui
 }
 
 }  // namespace fp8q
+
+// Whether 1x128 quantization takes two rows a thread, for the tests (no part
+// of the ABI).
+extern "C" int fp8q_quantize_few_rows(int64_t rows, int64_t cols) { return fp8q::takes_few_rows(rows, cols); }

@@ -15,3 +15,11 @@ def route(form, M, K, N):
     fn.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 3
     fn.restype = ctypes.c_int
     return NAMES[fn(FORMS[form], M, N, K)]
+
+
+def few_rows(rows, cols):
+    """Whether 1x128 quantization (plain layout) takes two rows a thread."""
+    fn = fp8q.lib().fp8q_quantize_few_rows
+    fn.argtypes = [ctypes.c_int64] * 2
+    fn.restype = ctypes.c_int
+    return bool(fn(rows, cols))

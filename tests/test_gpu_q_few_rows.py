@@ -1,7 +1,8 @@
 """The 1x128 quantizer's kernel for few elements against the oracle, byte for
 byte: one row, rows that do not fill a workgroup's eight, columns that do not
 fill its 512, padded rows in and out, both formats and scale rules, amaxes of
-zero and of tiny values; and the first size that takes the other kernel."""
+zero and of tiny values; and sizes just past its lines, which take the other
+kernel."""
 import numpy as np
 import pytest
 import torch
@@ -10,14 +11,18 @@ import oracle
 import paper_2609_22870_amd as fp8q
 from paper_2609_22870_amd import synth
 
+from _routes import few_rows
+
 pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("pow2,e5m2", [(False, False), (True, False), (False, True)])
-@pytest.mark.parametrize("rows,cols", [(1, 128), (7, 640), (9, 512), (33, 1152), (256, 4096), (131073, 128)])
+@pytest.mark.parametrize("rows,cols", [(1, 128), (7, 640), (9, 512), (33, 1152), (256, 4096), (8192, 128), (8193, 128),
+                                       (65537, 512)])
 def test_few_rows(rows, cols, pow2, e5m2):
+    assert few_rows(rows, cols) == (rows not in (8193, 65537))
     x = synth.activations(rows, cols, seed=951, outlier_seed=952)
     x[0, :64] = 0.0
     if rows > 5:
