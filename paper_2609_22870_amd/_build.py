@@ -42,22 +42,27 @@ def check_no_scratch(src, remarks):
                 raise RuntimeError("%s: %s spills to scratch (%d bytes per lane)" % (src, name, size))
 
 
-def build_native():
-    """_native.so: csrc/binding.cpp against the installed PyTorch's headers and
-    libraries (already loaded by the package's `import torch` when it is)."""
+def native_command(source, out, opt="-O2"):
+    """The compiler's command line for the binding's native code."""
     import sysconfig
 
     import torch
 
     t = os.path.dirname(torch.__file__)
+    return [os.environ.get("CXX", "g++"), opt, "-std=c++17", "-fPIC", "-shared", "-Wall",
+            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi()),
+            "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+            "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"),
+            "-isystem", sysconfig.get_paths()["include"], "-I", INCLUDE, source, "-o", out,
+            "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip"]
+
+
+def build_native():
+    """_native.so: csrc/binding.cpp against the installed PyTorch's headers and
+    libraries (already loaded by the package's `import torch` when it is)."""
     tmp = NATIVE + ".tmp%d" % os.getpid()
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi()),
-           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
-           "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"),
-           "-isystem", sysconfig.get_paths()["include"], "-I", INCLUDE, os.path.join(CSRC, "binding.cpp"), "-o", tmp,
-           "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip"]
+    cmd = native_command(os.path.join(CSRC, "binding.cpp"), tmp)
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("%s failed for binding.cpp:\n%s" % (cmd[0], r.stderr))

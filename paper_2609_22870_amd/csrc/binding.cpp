@@ -18,6 +18,8 @@
 #include <ATen/ops/empty.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <cxxabi.h>
+
 #include <cstring>
 
 #include "fp8q.h"
@@ -114,21 +116,31 @@ PyObject* pack(std::initializer_list<PyObject*> items) {
   return r;
 }
 
-struct Released {  // the GIL, for the library call
-  PyThreadState* s = PyEval_SaveThread();
-  ~Released() { PyEval_RestoreThread(s); }
-};
+// f() with the GIL released; f throws nothing.  Taken back by a call and not
+// by a destructor: in a daemon thread that returns while the interpreter shuts
+// down, PyEval_RestoreThread ends the thread by unwinding its stack, which a
+// destructor (noexcept) would turn into an abort of the process.
+template <typename F>
+auto unlocked(F&& f) {
+  PyThreadState* const s = PyEval_SaveThread();
+  const auto r = f();
+  PyEval_RestoreThread(s);
+  return r;
+}
 
 Api* api_of(PyObject* module) { return static_cast<Api*>(PyModule_GetState(module)); }
 
 // f(api, args), with everything it throws turned into "not an ordinary call"
-// (the Python code then meets the same condition and reports it).
+// (the Python code then meets the same condition and reports it), but for the
+// unwinding of a thread that ends (see unlocked), which must go on.
 template <Py_ssize_t N, typename F>
 PyObject* guarded(PyObject* module, PyObject* const* args, Py_ssize_t n, F&& f) {
   const Api* api = api_of(module);
   if (n == N && api->quantize) {
     try {
       return f(*api, args);
+    } catch (abi::__forced_unwind&) {
+      throw;
     } catch (...) {
       PyErr_Clear();
     }
@@ -152,11 +164,9 @@ PyObject* py_quantize(PyObject* m, PyObject* const* a, Py_ssize_t n) {
     uint8_t* cp = codes.mutable_data_ptr<uint8_t>();
     float* sp = scales.mutable_data_ptr<float>();
     ihipStream_t* s = stream_of(x);
-    fp8q_status st;
-    {
-      Released r;
-      st = api.quantize(xp, rows, cols, x.stride(0), g, flags, cp, codes.stride(0), sp, s);
-    }
+    const fp8q_status st = unlocked([&] {
+      return api.quantize(xp, rows, cols, x.stride(0), g, flags, cp, codes.stride(0), sp, s);
+    });
     if (st != FP8Q_OK) return PyLong_FromLong(st);
     return pack({give(a[3], codes), give(a[4], scales)});
   });
@@ -179,11 +189,9 @@ PyObject* py_quantize_dual(PyObject* m, PyObject* const* a, Py_ssize_t n) {
     uint8_t *crp = cr.mutable_data_ptr<uint8_t>(), *ctp = ct.mutable_data_ptr<uint8_t>();
     float *srp = sr.mutable_data_ptr<float>(), *stp = sct.mutable_data_ptr<float>();
     ihipStream_t* s = stream_of(x);
-    fp8q_status st;
-    {
-      Released r;
-      st = api.quantize_dual(xp, rows, cols, x.stride(0), flags, crp, cr.stride(0), srp, ctp, ct.stride(0), stp, s);
-    }
+    const fp8q_status st = unlocked([&] {
+      return api.quantize_dual(xp, rows, cols, x.stride(0), flags, crp, cr.stride(0), srp, ctp, ct.stride(0), stp, s);
+    });
     if (st != FP8Q_OK) return PyLong_FromLong(st);
     return pack({give(a[2], cr), give(a[3], sr), give(a[4], ct), give(a[5], sct)});
   });
@@ -238,14 +246,12 @@ PyObject* py_gemm(PyObject* m, PyObject* const* a, Py_ssize_t n) {
     const unsigned formats = POW2 ? 0u : (unsigned)integer(a[6]);
     const at::Tensor out = matrix_or_new(given, at::kBFloat16, p.M, p.N, p.device);
     void* cp = out.mutable_data_ptr();
-    fp8q_status st;
-    {
-      Released r;
-      st = POW2 ? api.gemm_pow2(p.a, p.sa, p.ga, p.lda, p.b, p.sb, p.gb, p.ldb, p.M, p.N, p.K, cp, out.stride(0),
+    const fp8q_status st = unlocked([&] {
+      return POW2 ? api.gemm_pow2(p.a, p.sa, p.ga, p.lda, p.b, p.sb, p.gb, p.ldb, p.M, p.N, p.K, cp, out.stride(0),
                                 p.stream)
                 : api.gemm_formats(p.a, p.sa, p.ga, p.lda, p.b, p.sb, p.gb, p.ldb, p.M, p.N, p.K, formats, cp,
                                    out.stride(0), p.stream);
-    }
+    });
     if (st != FP8Q_OK) return PyLong_FromLong(st);
     return give(given, out);
   });
@@ -261,12 +267,10 @@ PyObject* py_gemm_splitk(PyObject* m, PyObject* const* a, Py_ssize_t n) {
     const at::Tensor out = matrix_or_new(a[6], at::kBFloat16, p.M, p.N, p.device);
     void *cp = out.mutable_data_ptr(), *wp = ws.mutable_data_ptr();
     const int64_t bytes = ws.numel();
-    fp8q_status st;
-    {
-      Released r;
-      st = api.gemm_splitk(p.a, p.sa, p.ga, p.lda, p.b, p.sb, p.gb, p.ldb, p.M, p.N, p.K, cp, out.stride(0), wp, bytes,
+    const fp8q_status st = unlocked([&] {
+      return api.gemm_splitk(p.a, p.sa, p.ga, p.lda, p.b, p.sb, p.gb, p.ldb, p.M, p.N, p.K, cp, out.stride(0), wp, bytes,
                            p.stream);
-    }
+    });
     if (st != FP8Q_OK) return PyLong_FromLong(st);
     return give(a[6], out);
   });
@@ -282,12 +286,10 @@ PyObject* py_gemm_quantized(PyObject* m, PyObject* const* a, Py_ssize_t n) {
     const at::Tensor scales = vector_or_new(a[7], at::kFloat, ns, p.device);
     uint8_t* cp = codes.mutable_data_ptr<uint8_t>();
     float* sp = scales.mutable_data_ptr<float>();
-    fp8q_status st;
-    {
-      Released r;
-      st = api.gemm_quantized(p.a, p.sa, p.ga, p.lda, p.b, p.sb, p.gb, p.ldb, p.M, p.N, p.K, cp, codes.stride(0), sp,
+    const fp8q_status st = unlocked([&] {
+      return api.gemm_quantized(p.a, p.sa, p.ga, p.lda, p.b, p.sb, p.gb, p.ldb, p.M, p.N, p.K, cp, codes.stride(0), sp,
                               p.stream);
-    }
+    });
     if (st != FP8Q_OK) return PyLong_FromLong(st);
     return pack({give(a[6], codes), give(a[7], scales)});
   });
@@ -323,11 +325,9 @@ PyObject* py_gemm_grouped(PyObject* m, PyObject* const* a, Py_ssize_t n) {
       outs[i] = matrix_or_new(given ? PyList_GET_ITEM(a[3], i) : Py_None, at::kBFloat16, p.M, p.N, device);
       probs[i] = fp8q_gemm_problem{p.a, p.sa, p.lda, p.b, p.sb, p.ldb, outs[i].mutable_data_ptr(), outs[i].stride(0), p.M, p.N};
     }
-    fp8q_status st;
-    {
-      Released r;
-      st = api.gemm_grouped(probs, (int)count, ga, gb, K, stream);
-    }
+    const fp8q_status st = unlocked([&] {
+      return api.gemm_grouped(probs, (int)count, ga, gb, K, stream);
+    });
     if (st != FP8Q_OK) return PyLong_FromLong(st);
     if (given) {
       Py_INCREF(a[3]);
@@ -368,20 +368,21 @@ PyObject* py_calibrate_clip(PyObject* m, PyObject* const* a, Py_ssize_t n) {
     const int64_t bytes = ws.numel();
     ihipStream_t* s = stream_of(adv);
     if (a[10] != Py_True && a[10] != Py_False) leave();
-    fp8q_status st;
-    {
-      Released r;
-      st = api.calibrate_clip(in[0], in[1], in[2], in[3], in[4], tokens, l_old, h_old, config, wp, bytes, rp, s);
-    }
+    const fp8q_status st = unlocked([&] {
+      return api.calibrate_clip(in[0], in[1], in[2], in[3], in[4], tokens, l_old, h_old, config, wp, bytes, rp, s);
+    });
     if (st != FP8Q_OK) return PyLong_FromLong(st);
     if (a[10] == Py_False) Py_RETURN_TRUE;
     at::Tensor host;
-    try {
-      Released r;  // the copy waits for the kernels
-      host = result.reshape({-1}).slice(0, 0, kResult).cpu();
-    } catch (...) {  // the Python code reads it again and reports why
-      return give(a[9], result);
-    }
+    const bool read = unlocked([&] {  // the copy waits for the kernels
+      try {
+        host = result.reshape({-1}).slice(0, 0, kResult).cpu();
+        return true;
+      } catch (...) {
+        return false;
+      }
+    });
+    if (!read) return give(a[9], result);  // the Python code reads it again and reports why
     return PyBytes_FromStringAndSize(static_cast<const char*>(host.const_data_ptr()), kResult);
   });
 }
