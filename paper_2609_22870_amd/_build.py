@@ -2,6 +2,7 @@
 and _native.so (the binding's native code, host only) against PyTorch."""
 import os
 import subprocess
+import sys
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -66,7 +67,7 @@ def build_native():
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("%s failed for binding.cpp:\n%s" % (cmd[0], r.stderr))
-    r = subprocess.run(["python3", "-c", "import ctypes, sys, torch; ctypes.CDLL(sys.argv[1])", tmp],
+    r = subprocess.run([sys.executable, "-c", "import ctypes, sys, torch; ctypes.CDLL(sys.argv[1])", tmp],
                        capture_output=True, text=True)
     if r.returncode != 0:
         os.unlink(tmp)
@@ -97,7 +98,7 @@ def build():
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s" % r.stderr)
     # every symbol must resolve (a missing kernel stub only shows at load)
-    r = subprocess.run(["python3", "-c", "import ctypes, sys; ctypes.CDLL(sys.argv[1])", tmp],
+    r = subprocess.run([sys.executable, "-c", "import ctypes, sys; ctypes.CDLL(sys.argv[1])", tmp],
                        capture_output=True, text=True)
     if r.returncode != 0:
         os.unlink(tmp)
