@@ -26,8 +26,13 @@ int gemm_splitk_splits(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb
   return best;
 }
 
-// Workspace: one 32-bit counter per tile (the counters padded to 256
-// bytes), then `splits` fp32 partial tiles of 128 x 128 per tile.
+// Workspace: 256 bytes of counters (16 bits for each of the fewer than 128
+// tiles), then `splits` fp32 partial tiles of 128 x 128 per tile.  The place of
+// the counters is the same for every problem, so that a call's partial tiles
+// never lie where another problem's counters have to be zero.  The size is
+// that of 32-bit counters padded to 256 bytes: 256 bytes more than is used
+// from 65 tiles on.
+constexpr int64_t kSplitKCounterBytes = 256;
 int64_t gemm_splitk_workspace(int64_t M, int64_t N, int splits) {
   if (splits <= 1) return 0;
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
@@ -251,9 +256,8 @@ fp8q_status fp8q_gemm_splitk(const uint8_t* A, const float* sA, fp8q_granularity
     const int64_t need = fp8q::gemm_splitk_workspace(M, N, g.splits);
     if (!workspace || workspace_bytes < need) return FP8Q_ERR_INVAL;
     if (!aligned(workspace, 16)) return FP8Q_ERR_ALIGN;
-    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
     g.cnt = static_cast<uint32_t*>(workspace);
-    g.part = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + (tiles * 4 + 255) / 256 * 256);
+    g.part = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + fp8q::kSplitKCounterBytes);
   }
   return from_hip(fp8q::launch_gemm_splitk(g, pair, reinterpret_cast<hipStream_t>(stream)));
 }

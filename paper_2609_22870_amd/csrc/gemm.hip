@@ -353,10 +353,10 @@ __device__ __forceinline__ void store_quantized(const GemmArgs& g, const uint8_t
 // fp32 partial tile of their K range.  Each writes it to its slot of the
 // workspace (slot s of tile t at part + (t * splits + s) * BM * BN floats,
 // every wave's accumulators in register order, lane-interleaved in pairs),
-// then counts itself in cnt[t].  The workgroup that counts last reads all
+// then counts itself in the tile's 16 bits of cnt.  The workgroup that counts last reads all
 // the slots back and adds the partials in split order, ((p0 + p1) + p2) +
 // ..., so the sum does not depend on the order of arrival; it resets
-// cnt[t] to zero for the next call and goes on to the
+// the count to zero for the next call and goes on to the
 // epilogue, the others end.  Visibility across XCDs (each with its own L2)
 // without writing back or invalidating the L2s: the partials are stored
 // and loaded with agent-scope accesses (coherent at the device level), the
@@ -385,9 +385,11 @@ __device__ __forceinline__ bool splitk_reduce(const GemmArgs& g, v4f (&acc)[TI][
   __syncthreads();                                   // and every wave's
   __attribute__((address_space(3))) uint32_t* const flag = (__attribute__((address_space(3))) uint32_t*)flag_lds;
   if (threadIdx.x == 0) {
-    const uint32_t before = __hip_atomic_fetch_add(g.cnt + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const bool last = before == (uint32_t)(S - 1);
-    if (last) __hip_atomic_store(g.cnt + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t* const word = g.cnt + (tile >> 1);
+    const int shift = (tile & 1) * 16;
+    const uint32_t before = __hip_atomic_fetch_add(word, 1u << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = ((before >> shift) & 0xffffu) == (uint32_t)(S - 1);
+    if (last) __hip_atomic_fetch_sub(word, (uint32_t)S << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *flag = last ? 1u : 0u;
   }
   __syncthreads();

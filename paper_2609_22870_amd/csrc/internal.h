@@ -57,7 +57,7 @@ struct GemmArgs {
   int64_t ldq, cs_ld;
   // split-K (fp8q_gemm_splitk): `splits` workgroups share a tile, each
   // summing a contiguous range of K blocks; their fp32 partial tiles go to
-  // `part` and the last to arrive (counted in cnt[tile]) adds them up
+  // `part` and the last to arrive (counted in 16 bits of cnt) adds them up
   float* part = nullptr;
   uint32_t* cnt = nullptr;
   int splits = 1;

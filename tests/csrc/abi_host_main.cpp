@@ -143,6 +143,14 @@ int main() {
       fprintf(stderr, "split-K arguments: splits %d\n", fp8q::stub_gemm.splits);
       ++failures;
     }
+    // 120 tiles: the same place, where a workspace that both share has zeros
+    EXPECT(fp8q_gemm_splitk(cA, sA, FP8Q_BLOCK_1x128, 25600, cA, sA, FP8Q_BLOCK_128x128, 25600, 384, 5120, 25600, C,
+                            5120, ws, fp8q_gemm_splitk_workspace(384, 5120, 25600), nullptr),
+           FP8Q_OK, 1);
+    if (fp8q::stub_gemm.splits != 2 || (void*)fp8q::stub_gemm.part != (void*)(ws + 256)) {
+      fprintf(stderr, "split-K of 120 tiles: splits %d, partials elsewhere\n", fp8q::stub_gemm.splits);
+      ++failures;
+    }
     EXPECT(fp8q_gemm_splitk(cA, sA, FP8Q_BLOCK_1x128, 12288, cA, sA, FP8Q_BLOCK_128x128, 12288, 256, 4096, 12288, C,
                             4096, ws, ws_down - 1, nullptr),
            FP8Q_ERR_INVAL, 0);

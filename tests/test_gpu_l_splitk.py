@@ -22,6 +22,7 @@ import paper_2609_22870_amd as fp8q
 from paper_2609_22870_amd import synth
 
 import _par
+from _routes import route
 import test_gpu_b_gemm as tb
 import test_gpu_i_identity as ti
 
@@ -191,3 +192,21 @@ def test_splitk_padded_output(pair):
     b = synth.weights(N, K, seed=993, device=DEV)
     assert splits_of(M, N, K) == 4
     tb.run_pair(a, b, ga, gb, label="split-K padded " + pair, pad=6, gemm=fp8q.gemm_splitk, adds=3)
+
+
+def test_workspace_shared_by_tile_counts():
+    """A kept workspace serves problems of more and of fewer than 64 tiles in
+    turn (layers of one model): the partial tiles of one call do not lie where
+    another's counters are."""
+    cases = [(200, 16384, 4096), (162, 4096, 5504), (43, 32768, 3072), (250, 7168, 5120), (200, 16384, 4096)]
+    ws = torch.zeros(max(fp8q.gemm_splitk_workspace(M, N, K) for M, K, N in cases), dtype=torch.uint8, device=DEV)
+    for i, (M, K, N) in enumerate(cases):
+        print("shared workspace", (M, K, N), "S =", splits_of(M, N, K), flush=True)
+        assert route("splitk block", M, K, N) == "split-K"
+        A, sA, B, sB = _operands(M, K, N, seed=850 + 10 * i)
+        got = fp8q.gemm_splitk(A, sA, fp8q.BLOCK_1x128, B, sB, fp8q.BLOCK_128x128, workspace=ws,
+                               out=torch.full((M, N), 7.0, dtype=torch.bfloat16, device=DEV))
+        fresh = fp8q.gemm_splitk(A, sA, fp8q.BLOCK_1x128, B, sB, fp8q.BLOCK_128x128)
+        torch.cuda.synchronize()
+        assert torch.equal(got.view(torch.int16), fresh.view(torch.int16))
+        assert int(ws[:256].count_nonzero()) == 0, "counters not reset"
