@@ -26,6 +26,7 @@ import paper_2609_22870_amd as fp8q
 from paper_2609_22870_amd import synth
 
 import _par
+from _routes import route
 
 pytestmark = pytest.mark.gpu
 
@@ -105,11 +106,12 @@ def test_small_all_pairs(pair):
 
 @pytest.mark.parametrize("pair", list(PAIRS))
 def test_small_all_pairs_eight_wave_tiles(pair):
-    """Between 128 and 255 tiles of 128 x 128 (here 3 x 48, the last tile
+    """Between 128 and 256 tiles of 128 x 128 (here 3 x 48, the last tile
     row ragged): the eight-wave 128 x 128 kernel with four stages, one
     workgroup per CU (the 8B decode up-projection's path)."""
     ga, gb = PAIRS[pair]
     M, K, N = 272, 640, 6144
+    assert route(pair, M, K, N) == "eight waves"
     a = synth.activations(M, K, seed=181, outlier_seed=182, device=DEV)
     b = synth.weights(N, K, seed=183, device=DEV)
     run_pair(a, b, ga, gb, label=pair + " eight-wave tiles")
@@ -121,21 +123,36 @@ def test_small_all_pairs_k_groups(pair):
     over two groups of waves and sums their partial tiles (ragged M and,
     where the pair allows it, ragged N)."""
     ga, gb = PAIRS[pair]
-    M, K = 200, 1024
-    N = 384 if gb == fp8q.BLOCK_128x128 else 392
+    M, K = 190, 1024
+    N = 4096 if gb == fp8q.BLOCK_128x128 else 4104
+    assert route(pair, M, K, N) == "two K groups"
     a = synth.activations(M, K, seed=161, outlier_seed=162, device=DEV)
     b = synth.weights(N, K, seed=163, device=DEV)
-    run_pair(a, b, ga, gb, label=pair + " K groups")
+    run_pair(a, b, ga, gb, rows=_par.sample_rows(M, per_band=24), label=pair + " K groups")
+
+
+@pytest.mark.parametrize("M,K,N", [(200, 384, 1536), (300, 256, 4096)])
+@pytest.mark.parametrize("pair", list(PAIRS))
+def test_small_all_pairs_64x64(pair, M, K, N):
+    """The 64 x 64 kernel without K groups: an odd number of K blocks, and
+    more than 256 such tiles (ragged M and, where the pair allows it, N)."""
+    ga, gb = PAIRS[pair]
+    N += 0 if gb == fp8q.BLOCK_128x128 else 4
+    assert route(pair, M, K, N) == "small"
+    a = synth.activations(M, K, seed=171, outlier_seed=172, device=DEV)
+    b = synth.weights(N, K, seed=173, device=DEV)
+    run_pair(a, b, ga, gb, rows=_par.sample_rows(M, per_band=24), label=pair + " 64 x 64")
 
 
 @pytest.mark.parametrize("pair", ["tensor", "row"])
-@pytest.mark.parametrize("M,K,N", [(200, 256, 390), (16384 + 96, 128, 8192 + 6)])
+@pytest.mark.parametrize("M,K,N", [(200, 256, 390), (8192 + 96, 4096, 4096 + 6)])
 def test_ragged_columns_padded_output(pair, M, K, N):
     """N not a multiple of 4, so the last lane holding columns of a row has
     some of its four past N: those stay untouched in a padded output, the
     rest match the oracle.  The large shape runs the 256 x 256 kernel with a
     ragged last tile row and tile column (sampled rows plus the last ones)."""
     ga, gb = PAIRS[pair]
+    assert route(pair, M, K, N) == ("thin" if M == 200 else "large")
     a = synth.activations(M, K, seed=151, outlier_seed=152, device=DEV)
     b = synth.weights(N, K, seed=153, device=DEV)
     rows = None if M < 1024 else np.unique(np.concatenate([_par.sample_rows(M), np.arange(M - 20, M)]))
@@ -247,7 +264,8 @@ def test_many_tiles_ragged_blockwise():
     large-problem kernel takes several in turn (3185 tiles), with a ragged
     last tile row (M = 64 * 256 + 160) and a last tile column only half
     inside N (N = 97 * 128); the sampled rows include the last band."""
-    M, K, N = 16384 + 160, 256, 97 * 128
+    M, K, N = 16384 + 160, 2048, 97 * 128
+    assert route("block", M, K, N) == "large"
     a = synth.activations(M, K, seed=141, outlier_seed=142, device=DEV)
     b = synth.weights(N, K, seed=143, device=DEV)
     rows = np.unique(np.concatenate([_par.sample_rows(M), np.arange(M - 40, M)]))

@@ -12,6 +12,7 @@ import paper_2609_22870_amd as fp8q
 from paper_2609_22870_amd import synth
 
 import _par
+from _routes import route
 
 pytestmark = pytest.mark.gpu
 
@@ -78,9 +79,12 @@ def gemm_pow2_vs_oracle(x, w, rows=None, label=""):
                     tol=TOL, label=label)
 
 
-def test_gemm_small_tiles():
-    """Shapes that take each tile size, with ragged edges."""
-    for (M, K, N) in [(300, 512, 384), (5000, 384, 3072), (8352, 256, 4096)]:   # 64, 128, 256 tiles
+def test_gemm_every_kernel():
+    """Shapes that take each kernel, with ragged edges."""
+    for kernel, M, K, N in [("thin", 300, 512, 384), ("small", 200, 384, 1536), ("small", 300, 256, 4096),
+                            ("two K groups", 250, 512, 4096), ("eight waves", 300, 640, 6144),
+                            ("mid", 4000, 512, 2048), ("large", 8352, 2048, 4096)]:
+        assert route("pow2", M, K, N) == kernel
         x = synth.activations(M, K, seed=M, outlier_seed=M + 1, device=DEV)
         w = synth.weights(N, K, seed=N, device=DEV)
         rows = np.unique(np.concatenate([np.arange(0, M, max(1, M // 200)), np.arange(M - 8, M)]))

@@ -12,6 +12,7 @@ import paper_2609_22870_amd as fp8q
 from paper_2609_22870_amd import synth
 
 import _par
+from _routes import route
 from test_gpu_a_quantize import all_bf16_pairs
 
 pytestmark = pytest.mark.gpu
@@ -143,10 +144,13 @@ def run_formats(a_src, b_src, ga, gb, fa, fb, a_t=False, b_t=False, rows=None, l
 
 
 # (tokens, layer input width = dX columns, layer output width = contraction)
-@pytest.mark.parametrize("T,K_l,N_l", [(300, 384, 512), (5000, 3072, 384), (8352, 4096, 256)])  # 64, 128, 256 tiles
-def test_dgrad_e5m2_dy_all_tiles(T, K_l, N_l):
+@pytest.mark.parametrize("kernel,T,K_l,N_l", [
+    ("thin", 300, 384, 512), ("small", 200, 1536, 384), ("small", 300, 4096, 256), ("two K groups", 250, 4096, 512),
+    ("eight waves", 300, 6144, 640), ("mid", 4000, 2048, 512), ("large", 8352, 4096, 2048)])
+def test_dgrad_e5m2_dy_all_tiles(kernel, T, K_l, N_l):
     """dX[T, K_l] = dY[T, N_l] W[N_l, K_l]: A = dY in E5M2 (1x128), B = W^T
     (128x128, E4M3, written transposed)."""
+    assert route("block", T, N_l, K_l) == kernel
     dy = synth.grads(T, N_l, seed=T + 1, device=DEV)
     w = synth.weights(N_l, K_l, seed=N_l + 2, device=DEV)
     rows = np.unique(np.concatenate([np.arange(0, T, max(1, T // 160)), np.arange(T - 8, T)]))
@@ -154,13 +158,18 @@ def test_dgrad_e5m2_dy_all_tiles(T, K_l, N_l):
                 label="dgrad T=%d" % T)
 
 
-@pytest.mark.parametrize("T,K_l,N_l", [(512, 256, 384), (1024, 2048, 2560)])   # 64 and 128 tiles
-def test_wgrad_e5m2_dy(T, K_l, N_l):
+@pytest.mark.parametrize("kernel,T,K_l,N_l", [
+    ("thin", 512, 256, 384), ("small", 384, 208, 1536), ("two K groups", 512, 256, 4096), ("eight waves", 384, 304, 6144),
+    ("mid", 1024, 2048, 2560), ("large", 4096, 8288, 4096)])
+def test_wgrad_e5m2_dy(kernel, T, K_l, N_l):
     """dW^T[K_l, N_l] = X^T dY: A = X^T (E4M3), B = dY^T (E5M2), both grouped
     by 128 along the tokens and written transposed."""
+    assert route("blockk", K_l, T, N_l) == kernel
+    rows = None if K_l < 4096 else _par.sample_rows(K_l)
     x = synth.activations(T, K_l, seed=T + 3, outlier_seed=T + 4, device=DEV)
     dy = synth.grads(T, N_l, seed=T + 5, device=DEV)
-    run_formats(x, dy, fp8q.BLOCK_1x128, fp8q.BLOCK_1x128, 0, 1, a_t=True, b_t=True, label="wgrad T=%d" % T)
+    run_formats(x, dy, fp8q.BLOCK_1x128, fp8q.BLOCK_1x128, 0, 1, a_t=True, b_t=True, rows=rows,
+                label="wgrad T=%d" % T)
 
 
 def test_wgrad_dy_as_a():

@@ -13,12 +13,11 @@ of the zero products has no defined sign).  A's codes are random finite
 codes; they and the scales are inputs, so no FP8 quantization is involved
 (the quantizers are pinned byte for byte elsewhere).
 
-Shapes are chosen to reach each launch path: 256 x 256 tiles (at least 512
-of them; N = 4096 spans two odd 1024-column bands, which walk K backwards),
-128 x 128 tiles of four waves (at least 256 of them) and of eight waves
-(128 to 255 of them), 64 x 64 tiles with two K groups (an even number of K
-blocks on at most 256 tiles) and with one, and problems split into
-sub-launches because an operand spans 2 GiB (along N, and along M).  The
+Shapes are chosen to reach each launch path (and held to it): 256 x 256
+tiles (N = 4096 spans two odd 1024-column bands, which walk K backwards; the
+last round in 128 x 128 parts), 128 x 128 tiles of four waves and of eight,
+64 x 64 tiles with two K groups and with one, thin tiles, and problems split
+into sub-launches because an operand spans 2 GiB (along N, and along M).  The
 scales vary per row, column and block (no two neighbouring blocks alike by
 construction), so a scale read from the wrong row, column or K block
 shows."""
@@ -31,6 +30,7 @@ import paper_2609_22870_amd as fp8q
 from paper_2609_22870_amd import synth
 
 import _par
+from _routes import route
 
 pytestmark = pytest.mark.gpu
 
@@ -136,23 +136,32 @@ PAIRS = {
     "block": (fp8q.BLOCK_1x128, fp8q.BLOCK_128x128),
     "blockk": (fp8q.BLOCK_1x128, fp8q.BLOCK_1x128),
 }
-# (M, K, N): the launch path each reaches
-# (the (1x128, 1x128) pair has no 256 x 256 kernel: on the first shape it
-# runs its 128 x 128 kernel over many tiles)
+# (M, K, N): the launch path each reaches, every pair alike
 SHAPES = {
     "256x256 tiles": (8192 + 96, 4096, 4096),     # 33 x 16 = 528 big tiles, ragged last tile row
     "128x128 tiles": (4096 + 32, 1024, 1024),     # 33 x 8 = 264 mid tiles, 68 big ones
     "128x128 eight-wave tiles": (256 + 32, 6144, 6144),  # 3 x 48 = 144 mid tiles, 4 K bands
-    "64x64 two K groups": (160, 512, 512),        # 3 x 8 tiles, 4 K blocks
-    "64x64 one K group": (160, 384, 384),         # 3 K blocks
+    "64x64 two K groups": (300, 2048, 2048),      # 5 x 32 tiles, 16 K blocks, an odd band
+    "64x64 one K group": (350, 1920, 1536),       # 6 x 24 tiles, 15 K blocks, an odd band
+    "thin tiles": (160, 512, 512),                # 4 K blocks, fewer than waves
+    "thin tiles, odd K": (160, 1408, 384),        # 11 K blocks, a wave's second
 }
+ROUTES = {"256x256 tiles": "large", "128x128 tiles": "mid", "128x128 eight-wave tiles": "eight waves",
+          "64x64 two K groups": "two K groups", "64x64 one K group": "small", "thin tiles": "thin",
+          "thin tiles, odd K": "thin"}
+
+
+def shape_of(form, shape):
+    M, K, N = SHAPES[shape]
+    assert route(form, M, K, N) == ROUTES[shape]
+    return M, K, N
 
 
 @pytest.mark.parametrize("shape", list(SHAPES))
 @pytest.mark.parametrize("pair", list(PAIRS))
 def test_identity_every_kernel(pair, shape):
     ga, gb = PAIRS[pair]
-    M, K, N = SHAPES[shape]
+    M, K, N = shape_of(pair, shape)
     print("identity pin", pair, shape, (M, K, N), flush=True)
     c = Case(ga, gb, M, K, N, seed=1000 + 17 * list(PAIRS).index(pair) + list(SHAPES).index(shape))
     C = fp8q.gemm(c.A, c.sA, ga, c.B, c.sB, gb)
@@ -163,10 +172,11 @@ def test_identity_every_kernel(pair, shape):
 @pytest.mark.parametrize("pair", ["tensor", "row", "block", "blockk"])
 def test_identity_split_along_n(pair):
     """B spans more than 2 GiB (N = K = 46464): two sub-launches along N,
-    the first on 256 x 256 tiles (or 128 x 128), the second on 128 x 128
-    ones; B's scales are re-based at the split column."""
+    the first (45056 columns) on 256 x 256 tiles, the second on smaller ones;
+    B's scales are re-based at the split column."""
     ga, gb = PAIRS[pair]
     M, K, N = 2048 + 64, 46464, 46464
+    assert route(pair, M, K, 45056) == "large" and route(pair, M, K, N - 45056) != "large"
     print("identity pin split along N", pair, (M, K, N), flush=True)
     c = Case(ga, gb, M, K, N, seed=2000 + list(PAIRS).index(pair))
     C = fp8q.gemm(c.A, c.sA, ga, c.B, c.sB, gb)
@@ -196,7 +206,7 @@ def test_identity_split_along_m(pair):
 def test_identity_pow2_gemm(shape):
     """fp8q_gemm_pow2: the block scales enter the matrix instruction as
     exponents."""
-    M, K, N = SHAPES[shape]
+    M, K, N = shape_of("pow2", shape)
     print("identity pin pow2", shape, flush=True)
     c = Case(fp8q.BLOCK_1x128, fp8q.BLOCK_128x128, M, K, N, seed=4000 + list(SHAPES).index(shape))
     C = fp8q.gemm_pow2(c.A, c.sA, fp8q.BLOCK_1x128, c.B, c.sB, fp8q.BLOCK_128x128)
@@ -206,11 +216,10 @@ def test_identity_pow2_gemm(shape):
 
 @pytest.mark.parametrize("formats", [fp8q.A_E5M2, fp8q.B_E5M2, fp8q.A_E5M2 | fp8q.B_E5M2])
 @pytest.mark.parametrize("pair", ["block", "blockk"])
-@pytest.mark.parametrize("shape", ["256x256 tiles", "128x128 tiles", "128x128 eight-wave tiles",
-                                   "64x64 two K groups"])
+@pytest.mark.parametrize("shape", list(SHAPES))
 def test_identity_e5m2_formats(pair, formats, shape):
     ga, gb = PAIRS[pair]
-    M, K, N = SHAPES[shape]
+    M, K, N = shape_of(pair, shape)
     print("identity pin formats", pair, formats, shape, flush=True)
     c = Case(ga, gb, M, K, N, seed=5000 + 7 * formats + list(SHAPES).index(shape),
              e5m2_a=bool(formats & fp8q.A_E5M2), e5m2_b=bool(formats & fp8q.B_E5M2))
@@ -222,7 +231,10 @@ def test_identity_e5m2_formats(pair, formats, shape):
 @pytest.mark.parametrize("pair", ["tensor", "row", "block"])
 @pytest.mark.parametrize("ns,M", [((4096, 1024, 2048), 8192 + 96),    # 924 big tiles: 256 x 256
                                   ((1024, 512), 4096 + 32),            # 396 mid tiles: 128 x 128
-                                  ((256, 512, 128), 160)])             # 64 x 64, K groups
+                                  ((1920, 1536), 350),                 # 64 x 64 (15 K blocks)
+                                  ((2048,), 300),                      # K groups
+                                  ((2048, 256), 300),                  # K groups and thin, one launch
+                                  ((256, 512, 128), 160)])             # thin
 def test_identity_grouped(pair, ns, M):
     """One launch over problems that share A (and K), each with its own
     identity B of N_i rows and its own scales."""
@@ -238,11 +250,12 @@ def test_identity_grouped(pair, ns, M):
         check(C.cpu(), c.want(), "grouped %s problem %d" % (pair, i))
 
 
-@pytest.mark.parametrize("shape", ["256x256 tiles", "128x128 tiles"])
+@pytest.mark.parametrize("shape", list(SHAPES))
 def test_identity_quantized_output(shape):
     """fp8q_gemm_quantized: the exact bf16 output, quantized per 1x128 unit
     along N by the oracle, must come out byte for byte."""
     M, K, N = SHAPES[shape]
+    assert route("quantized", M, K, N) == {"small": "eight waves"}.get(ROUTES[shape], ROUTES[shape])
     print("identity pin quantized output", shape, flush=True)
     c = Case(fp8q.BLOCK_1x128, fp8q.BLOCK_128x128, M, K, N, seed=7000 + list(SHAPES).index(shape))
     codes, scales = fp8q.gemm_quantized(c.A, c.sA, fp8q.BLOCK_1x128, c.B, c.sB, fp8q.BLOCK_128x128)

@@ -1,8 +1,8 @@
 """Two runs of every kernel form give the same bytes (the outputs of a
 scaled GEMM are not unique within its tolerance, so run-to-run equality is
 asserted on its own): every GEMM launch path (256 x 256 tiles, 128 x 128 tiles of
-four and of eight waves, 64 x 64 tiles with and without two K groups) for every scaling
-pair, the power-of-two and E5M2 forms, the grouped GEMM and the GEMM with
+four and of eight waves, 64 x 64 tiles with and without two K groups, thin tiles) for every
+scaling pair, the power-of-two and E5M2 forms, the grouped GEMM and the GEMM with
 quantized output; every quantizer granularity plain and transposed
 (including the three-kernel tensor, column and transposed row passes), the
 dual-layout quantizer and the scale and format variants.  Real synthetic
@@ -12,6 +12,8 @@ import torch
 
 import paper_2609_22870_amd as fp8q
 from paper_2609_22870_amd import synth
+
+from _routes import route
 
 pytestmark = pytest.mark.gpu
 
@@ -27,9 +29,14 @@ SHAPES = {
     "256x256 tiles": (8192 + 96, 4096, 4096),
     "128x128 tiles": (4096 + 32, 1024, 1024),
     "128x128 eight-wave tiles": (256 + 32, 2048, 6144),
-    "64x64 two K groups": (160, 512, 512),
-    "64x64 one K group": (160, 384, 384),
+    "64x64 two K groups": (190, 1024, 4096),
+    "64x64 one K group": (200, 384, 1536),
+    "thin tiles": (160, 512, 512),
+    "thin tiles, odd K": (160, 1408, 384),
 }
+ROUTES = {"256x256 tiles": "large", "128x128 tiles": "mid", "128x128 eight-wave tiles": "eight waves",
+          "64x64 two K groups": "two K groups", "64x64 one K group": "small", "thin tiles": "thin",
+          "thin tiles, odd K": "thin"}
 
 
 def same(a, b):
@@ -49,6 +56,7 @@ def operands(M, K, N, ga, gb, seed, **kw):
 def test_gemm_twice(pair, shape):
     ga, gb = PAIRS[pair]
     M, K, N = SHAPES[shape]
+    assert route(pair, M, K, N) == ROUTES[shape]
     print("determinism gemm", pair, shape, flush=True)
     A, sA, B, sB = operands(M, K, N, ga, gb, seed=900 + list(SHAPES).index(shape))
     c1 = fp8q.gemm(A, sA, ga, B, sB, gb)
@@ -61,6 +69,7 @@ def test_gemm_twice(pair, shape):
 def test_variant_gemms_twice(shape):
     M, K, N = SHAPES[shape]
     print("determinism pow2 / e5m2 / quantized output", shape, flush=True)
+    assert all(route(f, M, K, N) == ROUTES[shape] for f in ("pow2", "block", "blockk"))
     A, sA, B, sB = operands(M, K, N, fp8q.BLOCK_1x128, fp8q.BLOCK_128x128, seed=920, pow2=True)
     runs = [fp8q.gemm_pow2(A, sA, fp8q.BLOCK_1x128, B, sB, fp8q.BLOCK_128x128) for _ in range(2)]
     torch.cuda.synchronize()
@@ -73,7 +82,8 @@ def test_variant_gemms_twice(shape):
         runs = [fp8q.gemm_formats(A, sA, ga, B, sB, gb, fp8q.A_E5M2 | fp8q.B_E5M2) for _ in range(2)]
         torch.cuda.synchronize()
         assert same(*runs), pair
-    if shape in ("256x256 tiles", "128x128 tiles"):
+    if ROUTES[shape] != "small":    # quantized output has no 64 x 64 tile
+        assert route("quantized", M, K, N) == ROUTES[shape]
         A, sA, B, sB = operands(M, K, N, fp8q.BLOCK_1x128, fp8q.BLOCK_128x128, seed=940)
         q1 = fp8q.gemm_quantized(A, sA, fp8q.BLOCK_1x128, B, sB, fp8q.BLOCK_128x128)
         q2 = fp8q.gemm_quantized(A, sA, fp8q.BLOCK_1x128, B, sB, fp8q.BLOCK_128x128)

@@ -3,17 +3,18 @@ decode step of the FP8 rollout: a few hundred activation rows against a
 whole weight).  Each 128 x 128 tile's K blocks are split over S workgroups
 whose fp32 partial tiles are added in split order by the last to arrive.
 
-* Parity against the oracle at the 8B decode down-projection (256 x 12288 x
-  4096, S = 4) and at small ragged shapes reaching S = 2, 4 and 8, for every
-  pair, to the bar of the other GEMM tests (tests/_par.py check_gemm, with
-  S - 1 more fp32 additions in the elementwise bound).
+* Parity against the oracle at ragged shapes that are split S = 2, 4 and 8
+  ways, for every pair, to the bar of the other GEMM tests (tests/_par.py
+  check_gemm, with S - 1 more fp32 additions in the elementwise bound); and
+  at shapes this entry point gives thin tiles, the 8B decode down-projection
+  (256 x 12288 x 4096) among them.
 * The exact identity pin (test_gpu_i_identity's construction: each output
   one exact product) through every split count: the partial sums and their
   sum are exact, so the output must match bit for bit.
-* The workspace protocol: the arrival counters are zero after every call;
-  one workspace serves calls of different split counts in a row; results
-  repeat bit for bit; a problem that is not split needs no workspace and
-  equals fp8q_gemm."""
+* The workspace protocol: a split writes its partial tiles there, and the
+  arrival counters are zero after every call; one workspace serves calls of
+  different split counts in a row; results repeat bit for bit; a problem that
+  is not split needs no workspace and equals fp8q_gemm."""
 import numpy as np
 import pytest
 import torch
@@ -30,9 +31,11 @@ pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
 PAIRS = tb.PAIRS
-# (M, K, N) -> S: 6 tiles of 128 x 128 with 8, 16, 32 K blocks; the last
-# tile row ragged (M = 200)
-SMALL = {2: (200, 1024, 384), 4: (200, 2048, 384), 8: (200, 4096, 384)}
+# S -> (M, K, N) of problems that a split takes less time for than thin
+# tiles; every last tile row ragged
+SPLIT = {2: (162, 4096, 5504), 4: (200, 16384, 4096), 8: (43, 32768, 3072)}
+# the same S by the workspace's rule, but thin tiles: 6 tiles of 128 x 128
+THIN = {2: (200, 1024, 384), 4: (200, 2048, 384), 8: (200, 4096, 384)}
 
 
 def splits_of(M, N, K):
@@ -46,38 +49,43 @@ def splits_of(M, N, K):
 
 
 def test_split_counts():
-    for s, (M, K, N) in SMALL.items():
-        assert splits_of(M, N, K) == s
+    for s in (2, 4, 8):
+        for (M, K, N), kernel in ((SPLIT[s], "split-K"), (THIN[s], "thin")):
+            assert splits_of(M, N, K) == s
+            assert all(route("splitk " + p, M, K, N) == kernel for p in PAIRS)
     assert splits_of(256, 4096, 12288) == 4
     assert splits_of(256, 12288, 4096) == 1
 
 
-@pytest.mark.parametrize("splits", list(SMALL))
+@pytest.mark.parametrize("kernel", ["split-K", "thin"])
+@pytest.mark.parametrize("splits", list(SPLIT))
 @pytest.mark.parametrize("pair", list(PAIRS))
-def test_splitk_small(pair, splits):
+def test_splitk_small(pair, splits, kernel):
     ga, gb = PAIRS[pair]
-    M, K, N = SMALL[splits]
+    M, K, N = (SPLIT if kernel == "split-K" else THIN)[splits]
     if gb != fp8q.BLOCK_128x128:
-        N += 4                       # ragged last tile column where the pair allows it
+        N -= 4                       # ragged last tile column where the pair allows it
+    assert splits_of(M, N, K) == splits and route("splitk " + pair, M, K, N) == kernel
     a = synth.activations(M, K, seed=701 + splits, outlier_seed=702, device=DEV)
     b = synth.weights(N, K, seed=703 + splits, device=DEV)
-    tb.run_pair(a, b, ga, gb, label="split-K S=%d %s" % (splits, pair), gemm=fp8q.gemm_splitk,
+    rows = np.append(np.arange(0, M, 11), M - 1) if kernel == "split-K" else None
+    tb.run_pair(a, b, ga, gb, rows=rows, label="%s S=%d %s" % (kernel, splits, pair), gemm=fp8q.gemm_splitk,
                 adds=splits - 1)
 
 
 def test_splitk_full_8b_decode_down():
-    """The 8B FFN down-projection of a decode step: 64 tiles, S = 4, every
-    row checked."""
+    """The 8B FFN down-projection of a decode step: 64 tiles, S = 4 by the
+    workspace's rule, thin tiles, every row checked."""
     shape = synth.WORKLOADS["8b_decode_blockwise"]["shapes"][1]
     M, K, N = shape
-    assert (M, K, N) == (256, 12288, 4096)
+    assert (M, K, N) == (256, 12288, 4096) and route("splitk block", M, K, N) == "thin"
     x = synth.activations(M, K, seed=synth.seed_for(4, 0, 1), outlier_seed=synth.seed_for(4, 3, 1), device=DEV)
     w = synth.weights(N, K, seed=synth.seed_for(4, 1, 1), device=DEV)
     tb.run_pair(x, w, fp8q.BLOCK_1x128, fp8q.BLOCK_128x128, label="split-K decode %s" % (shape,),
                 gemm=fp8q.gemm_splitk, adds=3)
 
 
-ID_SHAPES = {2: (160, 1024, 1024), 4: (200, 2048, 2048), 8: (200, 4096, 1024),
+ID_SHAPES = {2: (250, 7168, 5120), 4: (200, 16384, 4096), 8: (43, 32768, 3072),
              "decode down": (256, 12288, 4096)}
 
 
@@ -87,7 +95,8 @@ def test_splitk_identity(pair, shape):
     ga, gb = PAIRS[pair]
     M, K, N = ID_SHAPES[shape]
     print("split-K identity pin", pair, shape, (M, K, N), "S =", splits_of(M, N, K), flush=True)
-    assert splits_of(M, N, K) > 1
+    assert splits_of(M, N, K) == (4 if shape == "decode down" else shape)
+    assert route("splitk " + pair, M, K, N) == ("thin" if shape == "decode down" else "split-K")
     c = ti.Case(ga, gb, M, K, N, seed=3000 + 11 * list(PAIRS).index(pair) + list(ID_SHAPES).index(shape))
     C = fp8q.gemm_splitk(c.A, c.sA, ga, c.B, c.sB, gb)
     torch.cuda.synchronize()
@@ -103,24 +112,30 @@ def _operands(M, K, N, seed):
 
 
 def test_workspace_reuse_and_determinism():
-    """One zero-filled workspace, sized for the largest call, serves calls
-    with S = 4, 8, 2 and 4 again in a row; every result equals the same call
-    on a fresh workspace bit for bit, and the counters (the workspace's
-    first bytes) are zero after each call."""
-    cases = [(256, 12288, 4096), (200, 4096, 384), (200, 1024, 384), (256, 12288, 4096)]
+    """One workspace with zero counters, sized for the largest call, serves
+    calls with S = 4, 8, 2, thin tiles and S = 4 again in a row; every result
+    equals the same call on a fresh workspace bit for bit, a split wrote all
+    of its partial tiles (a thin call none), and the counters (the
+    workspace's first bytes) are zero after each call."""
+    cases = [SPLIT[4], SPLIT[8], SPLIT[2], (256, 12288, 4096), SPLIT[4]]
     need = max(fp8q.gemm_splitk_workspace(M, N, K) for M, K, N in cases)
     ws = torch.zeros(need, dtype=torch.uint8, device=DEV)
     for i, (M, K, N) in enumerate(cases):
-        print("workspace reuse", i, (M, K, N), "S =", splits_of(M, N, K), flush=True)
+        split = route("splitk block", M, K, N) == "split-K"
+        print("workspace reuse", i, (M, K, N), "S =", splits_of(M, N, K), "split", split, flush=True)
         A, sA, B, sB = _operands(M, K, N, seed=800 + 10 * i)
+        tiles = ((M + 127) // 128) * ((N + 127) // 128)
+        parts = ws[256:256 + tiles * splits_of(M, N, K) * 65536].view(torch.int32)
+        parts.fill_(0x7FC0A5A5)      # a NaN that no sum leaves
         got = fp8q.gemm_splitk(A, sA, fp8q.BLOCK_1x128, B, sB, fp8q.BLOCK_128x128, workspace=ws)
         fresh = fp8q.gemm_splitk(A, sA, fp8q.BLOCK_1x128, B, sB, fp8q.BLOCK_128x128)
         torch.cuda.synchronize()
         assert torch.equal(got.view(torch.int16), fresh.view(torch.int16))
-        tiles = ((M + 127) // 128) * ((N + 127) // 128)
-        assert int(ws[:4 * tiles].count_nonzero()) == 0, "counters not reset"
+        left = int((parts == 0x7FC0A5A5).sum())
+        assert left == (0 if split else parts.numel()), "partial tiles"
+        assert int(ws[:256].count_nonzero()) == 0, "counters not reset"
     # twice on the same inputs and workspace
-    A, sA, B, sB = _operands(256, 12288, 4096, seed=900)
+    A, sA, B, sB = _operands(*SPLIT[4], seed=900)
     c1 = fp8q.gemm_splitk(A, sA, fp8q.BLOCK_1x128, B, sB, fp8q.BLOCK_128x128, workspace=ws)
     c2 = fp8q.gemm_splitk(A, sA, fp8q.BLOCK_1x128, B, sB, fp8q.BLOCK_128x128, workspace=ws)
     torch.cuda.synchronize()
@@ -146,10 +161,12 @@ def test_graph_replays_and_side_stream():
     through the same workspace, on a stream of their own, in between: every
     replay gives the eager result bit for bit, and the counters are zero
     after each."""
-    M, K, N = 256, 12288, 4096
+    M, K, N = SPLIT[4]
+    M2, K2, N2 = SPLIT[8]
+    assert route("splitk block", M, K, N) == route("splitk block", M2, K2, N2) == "split-K"
     A, sA, B, sB = _operands(M, K, N, seed=970)
-    A2, sA2, B2, sB2 = _operands(200, 4096, 384, seed=980)
-    need = max(fp8q.gemm_splitk_workspace(M, N, K), fp8q.gemm_splitk_workspace(200, 384, 4096))
+    A2, sA2, B2, sB2 = _operands(M2, K2, N2, seed=980)
+    need = max(fp8q.gemm_splitk_workspace(M, N, K), fp8q.gemm_splitk_workspace(M2, N2, K2))
     ws = torch.zeros(need, dtype=torch.uint8, device=DEV)
     eager = fp8q.gemm_splitk(A, sA, fp8q.BLOCK_1x128, B, sB, fp8q.BLOCK_128x128, workspace=ws)
     torch.cuda.synchronize()
@@ -187,11 +204,12 @@ def test_splitk_padded_output(pair):
     only 8-byte aligned and the 8-byte store path runs), N not a multiple of
     4: the columns past N stay untouched, the rest match the oracle."""
     ga, gb = PAIRS[pair]
-    M, K, N = 200, 2048, 390
+    M, K, N = 200, 16384, 4090
     a = synth.activations(M, K, seed=991, outlier_seed=992, device=DEV)
     b = synth.weights(N, K, seed=993, device=DEV)
-    assert splits_of(M, N, K) == 4
-    tb.run_pair(a, b, ga, gb, label="split-K padded " + pair, pad=6, gemm=fp8q.gemm_splitk, adds=3)
+    assert splits_of(M, N, K) == 4 and route("splitk " + pair, M, K, N) == "split-K"
+    tb.run_pair(a, b, ga, gb, rows=np.append(np.arange(0, M, 11), M - 1), label="split-K padded " + pair, pad=6,
+                gemm=fp8q.gemm_splitk, adds=3)
 
 
 def test_workspace_shared_by_tile_counts():

@@ -3,7 +3,8 @@
 same library call: a tensor subclass (which the native code leaves alone)
 gives the same bytes as a plain tensor through every entry point, on a stream
 of its own too, and both routes report a refused call and a wrong buffer
-alike."""
+alike.  The native functions are counted: they take every call of a plain
+tensor and none of a subclass."""
 import pytest
 import torch
 
@@ -50,6 +51,20 @@ def calls(wrap):
     return out
 
 
+class Counted:
+    """The native functions, with the calls that they took and left."""
+
+    def __init__(self, native):
+        self.native, self.took, self.left = native, [], []
+
+    def __getattr__(self, name):
+        def call(*args):
+            r = getattr(self.native, name)(*args)
+            (self.left if r is None else self.took).append(name)
+            return r
+        return call
+
+
 def same(u, v):
     if isinstance(u, dict):
         return list(u) == list(v) and all(type(u[k]) is type(v[k]) and (u[k] == v[k]) for k in u)
@@ -60,10 +75,19 @@ def same(u, v):
 
 
 @pytest.mark.parametrize("own_stream", [False, True])
-def test_routes_agree(own_stream):
+def test_routes_agree(own_stream, monkeypatch):
+    counted = [Counted(fp8q._fast()), Counted(fp8q._fast())]
     with torch.cuda.stream(torch.cuda.Stream() if own_stream else torch.cuda.current_stream()):
-        native, python = calls(lambda t: t), calls(lambda t: t.as_subclass(Sub))
+        monkeypatch.setattr(fp8q, "_calls", counted[0])
+        native = calls(lambda t: t)
+        monkeypatch.setattr(fp8q, "_calls", counted[1])
+        python = calls(lambda t: t.as_subclass(Sub))
         torch.cuda.synchronize()
+    names = {"quantize", "quantize_dual", "gemm", "gemm_pow2", "gemm_splitk", "gemm_quantized", "gemm_grouped",
+             "calibrate_clip"}
+    # (without a workspace gemm_splitk is the Python code's, which makes one)
+    assert set(counted[0].took) == names and counted[0].left == ["gemm_splitk"]
+    assert set(counted[1].left) == names and not counted[1].took
     assert list(native) == list(python)
     for k in native:
         assert same(native[k], python[k]), k

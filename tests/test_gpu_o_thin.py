@@ -14,6 +14,7 @@ import torch
 import paper_2609_22870_amd as fp8q
 from paper_2609_22870_amd import synth
 
+from _routes import route
 from test_gpu_b_gemm import PAIRS, run_pair
 from test_gpu_h_grouped import check_group
 from test_gpu_l_splitk import splits_of
@@ -33,6 +34,7 @@ def test_thin_against_oracle(pair, shape):
     M, K, N = shape
     if gb != B128:
         N -= 6                                   # ragged columns where the pair allows them
+    assert route(pair, M, K, N) == "thin"
     a = synth.activations(M, K, seed=801, outlier_seed=802, device=DEV)
     b = synth.weights(N, K, seed=803, device=DEV)
     run_pair(a, b, ga, gb, rows=np.unique(np.append(np.arange(0, M, 1 + M // 40), M - 1)), label="thin %s" % pair,
@@ -46,6 +48,7 @@ def test_thin_pow2_and_formats(shape):
     roundings of the sums; E5M2 codes in A, B or both: equal to E4M3 codes
     of the same values where both formats hold them."""
     M, K, N = shape
+    assert all(route(f, M, K, N) == "thin" for f in ("pow2", "block", "blockk"))
     a = synth.activations(M, K, seed=811, outlier_seed=812, device=DEV)
     b = synth.weights(N, K, seed=813, device=DEV)
     A, sA = fp8q.quantize(a, B1, pow2=True)
@@ -58,7 +61,6 @@ def test_thin_pow2_and_formats(shape):
     e = torch.randint(0, 4, (M + N, K), generator=g, device=DEV, dtype=torch.uint8)
     sign = torch.randint(0, 2, (M + N, K), generator=g, device=DEV, dtype=torch.uint8) * 0x80
     e4, e5 = (0x38 + e * 8) | sign, (0x3C + e * 4) | sign
-    want = {}
     for pair, gb in (("block", B128), ("blockk", B1)):
         sb = torch.ones(fp8q.scales_count(N, K, gb), dtype=torch.float32, device=DEV)
         sa = torch.ones(fp8q.scales_count(M, K, B1), dtype=torch.float32, device=DEV)
@@ -74,6 +76,7 @@ def test_thin_quantized_output(shape):
     """The quantized output is the quantizer's on the plain call's output,
     bit for bit (both sum in the thin tiles' order)."""
     M, K, N = shape
+    assert route("quantized", M, K, N) == "thin"
     A, sA = fp8q.quantize(synth.activations(M, K, seed=841, outlier_seed=842, device=DEV), B1)
     B, sB = fp8q.quantize(synth.weights(N, K, seed=843, device=DEV), B128)
     codes = torch.full((M, N + 128), 0x55, dtype=torch.uint8, device=DEV)
@@ -97,7 +100,7 @@ def test_thin_grouped(M, K):
 def test_split_still_chosen(pair, shape):
     splits, M, K, N = shape
     ga, gb = PAIRS[pair]
-    assert splits_of(M, N, K) == splits
+    assert splits_of(M, N, K) == splits and route("splitk " + pair, M, K, N) == "split-K"
     a = synth.activations(M, K, seed=831, outlier_seed=832, device=DEV)
     b = synth.weights(N, K, seed=833, device=DEV)
     run_pair(a, b, ga, gb, rows=np.arange(3, M, 23), label="split-K S=%d %s" % (splits, pair), gemm=fp8q.gemm_splitk,
