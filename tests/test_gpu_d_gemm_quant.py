@@ -30,6 +30,7 @@ import paper_2609_22870_amd as fp8q
 from paper_2609_22870_amd import synth
 
 import _par
+from _routes import route
 
 pytestmark = pytest.mark.gpu
 
@@ -174,15 +175,23 @@ def _unit_check():
     return _UNIT_CHECK
 
 
-def test_small_several_tiles_ragged():
-    M, K, N = 300, 512, 384
+# (M, K, N) that take each kernel below the 256 x 256 tiles, the last tile row ragged
+SMALL = {"thin": (300, 512, 384), "two K groups": (190, 512, 4096), "eight waves": (200, 384, 1536),
+         "mid": (4000, 512, 2048)}
+
+
+@pytest.mark.parametrize("kernel", list(SMALL))
+def test_small_several_tiles_ragged(kernel):
+    M, K, N = SMALL[kernel]
+    assert route("quantized", M, K, N) == kernel
     x = synth.activations(M, K, seed=151, outlier_seed=152, device=DEV)
     w = synth.weights(N, K, seed=153, device=DEV)
-    fused_vs_oracle(x, w, np.arange(M), "small ragged")
+    fused_vs_oracle(x, w, np.unique(np.append(np.arange(0, M, 1 + M // 400), M - 1)), "small ragged " + kernel)
 
 
-def test_padded_codes_and_determinism():
-    M, K, N = 256, 256, 256
+@pytest.mark.parametrize("kernel", list(SMALL))
+def test_padded_codes_and_determinism(kernel):
+    M, K, N = SMALL[kernel]
     x = synth.activations(M, K, seed=161, outlier_seed=162, device=DEV)
     w = synth.weights(N, K, seed=163, device=DEV)
     A, sA = fp8q.quantize(x, fp8q.BLOCK_1x128)

@@ -65,7 +65,8 @@ def test_mixed_tiled_and_k_group_problems():
     x1 = synth.activations(4096, 512, seed=211, outlier_seed=212, device=DEV)
     x2 = synth.activations(192, 512, seed=213, outlier_seed=214, device=DEV)
     w1 = synth.weights(2048, 512, seed=215, device=DEV)
-    w2 = synth.weights(384, 512, seed=216, device=DEV)
+    w2 = synth.weights(4096, 512, seed=216, device=DEV)
+    assert route("block", 4096, 512, 2048) == "mid" and route("block", 192, 512, 4096) == "two K groups"
     check_group([x1, x2], [w1, w2], fp8q.BLOCK_1x128, fp8q.BLOCK_128x128, rows=_par.sample_rows(192),
                 label="mixed tiled and K groups")
 
@@ -97,9 +98,11 @@ def test_distinct_inputs_and_sizes():
 
 
 def test_eight_problems_128_tiles():
-    """FP8Q_MAX_GROUP problems, enough tiles for the 128 x 128 tile."""
-    x = synth.activations(2048, 256, seed=241, outlier_seed=242, device=DEV)
-    ws = [synth.weights(512, 256, seed=243 + i, device=DEV) for i in range(fp8q.MAX_GROUP)]
+    """FP8Q_MAX_GROUP problems, alone on 64 x 64 tiles, together enough tiles
+    for the 128 x 128 tile (512)."""
+    assert route("block", 2048, 384, 512) == "small"
+    x = synth.activations(2048, 384, seed=241, outlier_seed=242, device=DEV)
+    ws = [synth.weights(512, 384, seed=243 + i, device=DEV) for i in range(fp8q.MAX_GROUP)]
     check_group([x] * fp8q.MAX_GROUP, ws, fp8q.BLOCK_1x128, fp8q.BLOCK_128x128,
                 rows=_par.sample_rows(2048), label="eight")
 
