@@ -274,10 +274,10 @@ int64_t fp8q_gemm_splitk_workspace(int64_t M, int64_t N, int64_t K);
  * fp8q_gemm for skinny problems such as a decode step of the FP8 rollout
  * (Sec. 2.3, Sec. 5: a few hundred rows of activations against a full
  * weight), where the 128 x 128 tiles of C are too few to give every CU one
- * (fewer than 128).  The K blocks of each tile are split over S workgroups (S a power
- * of two up to 8, S x tiles <= 256, at least four K blocks each), so that
- * each CU streams 1/S of the tile's operand rows; the S fp32 partial tiles
- * are added in a fixed order, then rounded to bf16 once.  Where small tiles
+ * (fewer than 128).  The K blocks of each tile are split over S workgroups (S
+ * a power of two up to 8, S x tiles <= 256, at least four K blocks each), so
+ * that each CU streams 1/S of the tile's operand rows; the S fp32 partial
+ * tiles are added in a fixed order, then rounded to bf16 once.  Where small tiles
  * whose waves split K inside one workgroup take less time, they run instead
  * (the workspace rules stay those of the split).  The product,
  * pairs, layouts, shape and alignment rules are those of fp8q_gemm, and
@@ -288,8 +288,9 @@ int64_t fp8q_gemm_splitk_workspace(int64_t M, int64_t N, int64_t K);
  * workspace: device memory of at least fp8q_gemm_splitk_workspace(M, N, K)
  * bytes (workspace_bytes), 16-byte aligned, ZERO-FILLED before its first
  * use; it holds per-tile arrival counters, which every call leaves at
- * zero, and the partial tiles.  Calls that share a workspace must not
- * overlap (issue them on one stream).  Errors: those of fp8q_gemm; a null
+ * zero, and the partial tiles.  One workspace serves problems of any sizes
+ * in turn; calls that share it must not overlap (issue them on one
+ * stream).  Errors: those of fp8q_gemm; a null
  * or short workspace when the call splits -> INVAL, misaligned -> ALIGN.
  */
 fp8q_status fp8q_gemm_splitk(const uint8_t *A, const float *sA,

@@ -6,13 +6,15 @@
 // both the depth of one v_mfma_f32_16x16x128_f8f6f4 and the length of one
 // scale block, so a blockwise step is one MFMA per 16 x 16 tile into a
 // zeroed partial, then one FMA per accumulator that adds S_A * S_B * P.
-// Five shapes are built: 256 x 256 tiles with eight waves of 128 x 64 (the
-// large-problem kernel: 64 FP8 bytes of LDS traffic per MFMA instead of
-// 128), 128 x 256 tiles with eight waves of 64 x 64 (parts of its last
-// round, see large_tiles), 128 x 128 tiles with four waves of 64 x 64 (small
-// grids), and for skinny problems such as a decode step, 128 x 128 tiles with eight
-// waves of 32 x 64 and 64 x 64 tiles with four waves of 32 x 32, where a
-// few tiles split their K blocks over two groups of waves.
+// Five shapes share their waves' work this way: 256 x 256 tiles with eight
+// waves of 128 x 64 (the large-problem kernel: 64 FP8 bytes of LDS traffic per
+// MFMA instead of 128), 128 x 256 tiles with eight waves of 64 x 64 (parts of
+// its last round, see large_tiles), 128 x 128 tiles with four waves of 64 x 64
+// (small grids), and for skinny problems such as a decode step, 128 x 128
+// tiles with eight waves of 32 x 64 and 64 x 64 tiles with four waves of 32 x
+// 32, where a few tiles split their K blocks over two groups of waves.  Thin
+// tiles of 16 x 16 to 64 x 64 give every wave K blocks of its own (see
+// thin_tile).  dispatch.h says which problem takes which.
 //
 // Operand tiles (rows x 128 bytes of K) go global -> LDS with the
 // direct-to-LDS 16-byte buffer loads of gfx950 (no VGPR staging), in a ring
@@ -633,8 +635,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint8_t* lds_all, i
   constexpr int kPerStripB = (kPerB + TI / 2 - 1) / (TI / 2);        // strips TI/2 .. TI-1
   static_assert(kQ <= kWaves, "at most one scale-vector load per wave and step");
   // LDS reads of the step's scales, issued after the first strip's MFMAs
-  constexpr int kScaleReads = PAIR == kPairBlock ? TI + 1 : (PAIR == kPairBlockK ? TJ + 2 : 0);
-  static_assert(kScaleReads + 2 <= 15, "outstanding LDS reads must fit the lgkm counter");
+  // (1x128 x 1x128: the column scales, two row scales and a fragment at most)
+  constexpr int kScaleReads = PAIR == kPairBlock ? TI + 1 : 0;
+  static_assert((PAIR == kPairBlockK ? TJ + 2 : kScaleReads) + 2 <= 15, "outstanding LDS reads must fit the lgkm counter");
 
   // One K step; kMore: the loads of stage kt + kStages - 1 go out during
   // it (all but the last kStages - 1 steps, which run without, so that no
@@ -1299,11 +1302,11 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KS) void gemm_kernel(G
 // of kCUs, or every tile) therefore take a part of a tile each: the tiles at
 // raster positions full, full + 1, ... are cut into `parts` = 4 of 128 x 128
 // (eight waves of 32 x 64) or 2 of 128 x 256 (eight waves of 64 x 64), which
-// run on 4 or 2 times as many CUs for 0.4 or 0.62 of a tile's time (measured:
-// one round of each at K = 4096, 19, 33 and 56 us; blockwise 3001 x 5120 x
-// 17408, 3.2 rounds, 268 -> 242 us; power-of-two scales 4096 x 5120 x 17408,
-// 4.25 rounds, 321 -> 301 us; 2048 x 4096 x 12288, 1.5 rounds, 105 us on 128
-// x 128 tiles -> 95 us).  Every tile shape sums an output's K blocks in the
+// run on 4 or 2 times as many CUs for 0.34 or 0.59 of a tile's time (one round
+// of each at K = 4096: 19, 33 and 56 us; blockwise 3001 x 5120 x 17408, 3.2
+// rounds, 268 -> 242 us; power-of-two scales 4096 x 5120 x 17408, 4.25 rounds,
+// 321 -> 301 us; 2048 x 4096 x 12288, 1.5 rounds, 105 us on 128 x 128 tiles ->
+// 95 us).  Every tile shape sums an output's K blocks in the
 // same order, so the cut changes no bit.
 
 template <int PAIR>
@@ -1702,7 +1705,7 @@ hipError_t launch_grouped_large(GemmGroup gs, hipStream_t s) {
 // The problems with two K groups and the thin ones in one launch, where their
 // 64 x 64 tiles together are one round of the CUs; hipErrorNotSupported where
 // not.  Two launches of part of the chip each, one after the other, take
-// longer (192 tokens, 4096 x (4096 + 256 + 256): 15.2 us, here 11.2).
+// longer (192 tokens, 4096 x (4096 + 256 + 256): 15.4 us, here 11.0).
 template <int PAIR>
 hipError_t launch_grouped_mixed(GemmGroup grouped, GemmGroup thin, hipStream_t s) {
   const int64_t a = count_tiles<64, 64>(grouped), b = count_tiles<64, 64>(thin);
@@ -1714,11 +1717,15 @@ hipError_t launch_grouped_mixed(GemmGroup grouped, GemmGroup thin, hipStream_t s
 // Each problem goes to the kernel a single call would give it.  The tiled
 // kernels without K groups all sum K in one order, so one launch takes every
 // problem a single call would give one of them (the tile size from their
-// tile count over all, as launch_pair chooses it for one: for a skinny
-// problem among large ones that is a larger tile than its own, with the same
-// bits); the problems a single call would give the thin tiles (which sum in
-// an order of their own, whatever their size) go to a second launch, and
-// those it would split into K groups to a third.
+// tile count over all: 256 x 256 as takes_large says, 128 x 128 of four waves
+// from 256 of them on, else 64 x 64; of a single call's kernels the eight-wave
+// one is missing; for a skinny problem among large ones the tile is larger
+// than its own, with the same bits); the problems a single call would give
+// the thin tiles (which sum in an order of their own, whatever their size) and
+// those it would split into K groups go to a second launch, or one each (see
+// launch_grouped_mixed).  The thin order is kept where many problems make it
+// the slower one: 512 tokens, 8 x (1024 x 1024) 19.9 us, in two K groups 18.7;
+// 64 tokens, 3 x (4096 x 4096) 13.1 and 11.6.
 template <int PAIR>
 hipError_t launch_grouped_pair(const GemmGroup& gs, hipStream_t s) {
   GemmGroup tiled{}, thin{}, grouped{};
