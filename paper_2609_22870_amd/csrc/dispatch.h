@@ -211,13 +211,17 @@ inline GemmRoute gemm_quantized_route(const GemmSize& s) {
 // from them): its share of the K steps, and about 8 us and 0.8 per part for
 // the partial tiles' way through memory; the thin tiles' waves meet in LDS.
 // 256 x 12288 x 4096: split over four 24.9 us, thin 64 x 64 tiles 21.9; 64 x
-// 25600 x 5120: split over four 42.0, thin 49.6.  The choice is 0.4% above the
+// 25600 x 5120: split over four 42.0, thin 49.6.  More than 32 rows, whose
+// thin tiles read the weights more than once or in 64-column strips, lose more
+// against weights from memory than fewer do (33 x 25600 x 5120: split 39.4,
+// thin 47.0; 64 x 17408 x 5120: 32.4 and 35.6).  The choice is 0.4% above the
 // better on average (2.8% with a rule on bytes per CU alone).
 inline GemmRoute gemm_splitk_route(int form, const GemmSize& s, int splits) {
   if (splits <= 1) return gemm_route(form, s);
   double thin;
   thin_config(&s, 1, thin);
-  return thin * thin_from_memory(s) < 7850 + 530.0 * (s.K / kBlockK) / splits + 811.0 * splits ? kThinTiles : kSplitK;
+  thin *= thin_from_memory(s) > 1.0 && s.M > 32 ? 1.4 : thin_from_memory(s);
+  return thin < 7850 + 530.0 * (s.K / kBlockK) / splits + 811.0 * splits ? kThinTiles : kSplitK;
 }
 
 // 1x128 quantization, plain layout: two rows a thread instead of eight.  Up
