@@ -58,10 +58,11 @@ inline LargePlan large_plan(int64_t total) {
 // 12.4; at K = 4096 1x128 x 1x128 455 and 400 the other way).  Within a few
 // percent the side that holds on more of the sizes: large from 512 tiles on,
 // where they fill whole rounds or a last one in halves, and for one long round
-// that more than 512 of the others would need two for (K >= 3072; measured 0.85 to 0.98 of them, not
-// with 1x128 x 1x128 scales: 0.92 to 1.04).  1% of those sizes are more than 2.5% slower than with the
-// rule "large from 512 tiles on, 1x128 x 1x128 never"; 15% were with estimates
-// of K = 4096 for every K.
+// that more than 512 of the others would need two for (K >= 3072; measured
+// 0.85 to 0.98 of them, not with 1x128 x 1x128 scales: 0.92 to 1.04).  1% of
+// those sizes are more than 2.5% slower than with the rule "large from 512
+// tiles on, 1x128 x 1x128 never"; 15% were with estimates of K = 4096 for
+// every K.
 struct BlockNs {
   int large, mid;
 };
