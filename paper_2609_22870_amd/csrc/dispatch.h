@@ -62,16 +62,21 @@ inline LargePlan large_plan(int64_t total) {
 // 0.85 to 0.98 of them, not with 1x128 x 1x128 scales: 0.92 to 1.04).  1% of
 // those sizes are more than 2.5% slower than with the rule "large from 512
 // tiles on, 1x128 x 1x128 never"; 15% were with estimates of K = 4096 for
-// every K.
+// every K.  Those were bursts on codes of random bits; run for long on
+// quantized normal values, at the clock that the power limit holds, the 128 x
+// 128 tiles take up to 3% longer beside the large ones with 1x128 x 1x128
+// scales and quantized output (6528 x 1280 x 16384 178 us, large 168; 2500 x
+// 2048 x 8192 quantized 55.1 and 51.8), and their times per K block here are
+// those.
 struct BlockNs {
   int large, mid;
 };
 constexpr BlockNs kBlockNs[6] = {{1614, 892},   // tensor
                                  {1614, 892},   // row
                                  {1814, 1031},  // 1x128 x 128x128
-                                 {2204, 1152},  // 1x128 x 1x128
+                                 {2204, 1180},  // 1x128 x 1x128
                                  {1708, 983},   // power-of-two scales
-                                 {1944, 1072}}; // quantized output
+                                 {1944, 1100}}; // quantized output
 // forms: the GemmPair values, then
 constexpr int kFormQuantized = 5;
 

@@ -36,6 +36,9 @@ def test_short_k_stays_off_large_tiles(form):
     if form == "blockk":
         for M, N in ((8192, 4096), (16384, 6144), (16384, 12288), (4096, 17408)):
             assert [route(form, M, K, N) for K in (128, 512, 16384)] == ["mid", "mid", "large"], (M, N)
+        assert route(form, 6528, 1280, 16384) == route(form, 4096, 1280, 17408) == "large"  # on mid 6% longer
+    if form == "quantized":
+        assert route(form, 2500, 2048, 8192) == "large"  # on mid 6% longer
 
 
 def test_quantized_output_sums_as_the_plain_call():
